@@ -182,6 +182,8 @@ __device__ __forceinline__ bool exp_one_tangent(const double th[4], int tau, Mat
 __device__ __forceinline__ void exp_half_tangent(const double th[4], int /*tau*/, Mat<2>& E,
                                                  Mat<2>& dEx, Mat<2>& dEy) {
   exp_half(th, 0, E);
+  E.r[0][0] += 1.0;
+  E.r[1][1] += 1.0;
   const double t2 = fma(th[0], th[0], fma(th[1], th[1], th[2] * th[2]));
   const double big = sqrt(t2);
   const double x = 0.5 * big;

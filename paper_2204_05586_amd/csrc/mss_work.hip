@@ -71,7 +71,7 @@ struct TableSource {
   }
 };
 
-__global__ void __launch_bounds__(256) work_integrate_kernel(const IntegrateWorkArgs A) {
+__global__ void __launch_bounds__(256, 2) work_integrate_kernel(const IntegrateWorkArgs A) {
   work_integrate_loop(A, TableSource{});
 }
 
