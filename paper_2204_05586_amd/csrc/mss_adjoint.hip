@@ -11,8 +11,8 @@
 //      from (psi_{k+1}, lambda_{k+1}) in frame coordinates, recovering the
 //      state before each exponential as E^H psi (E is unitary), take
 //      dloss/dtheta = 2 Re(lambda^H dE/dtheta psi_before) with dE/dtheta
-//      from tangent residual squarings (the derivative of exactly the
-//      computed exponential), then apply the chain rule through the CF4
+//      the derivative of exactly the computed exponential, in closed form or
+//      from tangent residual squarings, then apply the chain rule through the CF4
 //      weights, the frame rotation of the transverse field and the field
 //      terms; gradients are summed per segment in registers and added to
 //      the output with FP64 atomics.
@@ -181,26 +181,31 @@ __device__ __forceinline__ bool exp_one_tangent(const double th[4], int tau, Mat
 // dE/dtheta_dir for dir = x, y.
 __device__ __forceinline__ void exp_half_tangent(const double th[4], int /*tau*/, Mat<2>& E,
                                                  Mat<2>& dEx, Mat<2>& dEy) {
+  double u, c, S;
   exp_half(th, 0, E);
   E.r[0][0] += 1.0;
   E.r[1][1] += 1.0;
-  const double t2 = fma(th[0], th[0], fma(th[1], th[1], th[2] * th[2]));
-  const double big = sqrt(t2);
-  const double x = 0.5 * big;
-  // c = cos(T/2), S = sin(T/2)/T with T = |theta|:
-  //   dc/dtheta_a = -(S/2) theta_a,  dS/dtheta_a = (c/2 - S)/T^2 theta_a,
-  // the latter by its series (1/8)(-1/3 + x^2/30 - x^4/840), x = T/2, when small.
-  double c, S, dS_over;
-  if (x < 0x1p-7) {
-    const double x2 = x * x;
-    c = fma(x2, fma(x2, fma(x2, -1.0 / 720.0, 1.0 / 24.0), -0.5), 1.0);
-    S = 0.5 * fma(x2, fma(x2, 1.0 / 120.0, -1.0 / 6.0), 1.0);
-    dS_over = 0.125 * fma(x2, fma(x2, -1.0 / 840.0, 1.0 / 30.0), -1.0 / 3.0);
+  half_coefficients(th, u, c, S);
+  // c = cos(T/2), S = sin(T/2)/T with T = |theta|: dc/dtheta_a = -(S/2) theta_a
+  // and dS/dtheta_a = (c/2 - S)/T^2 theta_a, by its series in u = T^2 / 4
+  // where the difference cancels: sum_k (-1)^k k u^(k-1) / (4 (2k+1)!).
+  double dS_over;
+  if (u <= 0x1p-8) {
+    dS_over = fma(u, fma(u, fma(u, fma(u, -1.25 / 39916800, 1.0 / 362880), -0.75 / 5040),
+                         0.5 / 120), -0.25 / 6);
+  } else if (u <= 1.0) {
+    double ps = 2.5 / 51090942171709440000.0;  // 21!
+    ps = fma(-ps, u, 2.25 / 121645100408832000.0);
+    ps = fma(-ps, u, 2.0 / 355687428096000.0);
+    ps = fma(-ps, u, 1.75 / 1307674368000.0);
+    ps = fma(-ps, u, 1.5 / 6227020800.0);
+    ps = fma(-ps, u, 1.25 / 39916800.0);
+    ps = fma(-ps, u, 1.0 / 362880.0);
+    ps = fma(-ps, u, 0.75 / 5040.0);
+    ps = fma(-ps, u, 0.5 / 120.0);
+    dS_over = -fma(-ps, u, 0.25 / 6.0);
   } else {
-    double s;
-    sincos_cw(x, &s, &c);
-    S = s / big;
-    dS_over = (0.5 * c - S) / t2;
+    dS_over = (0.5 * (1.0 + c) - S) / (4.0 * u);
   }
   const double dc_over = -0.5 * S;
 #pragma unroll
@@ -296,25 +301,126 @@ template <> struct TangentStep<2> {
     mat_h_vec<2>(E, lr, li, nlr, nli);
   }
 };
+// The step through the tangent squarings: any tau and any angles.
+__device__ __forceinline__ void tangent_step_squarings(const double th[4], int tau,
+                                                       const double* lr, const double* li,
+                                                       const double* pr, const double* pi,
+                                                       double* br, double* bi, double* nlr,
+                                                       double* nli, double* gx, double* gy) {
+  Mat<3> E, G;
+  double c[4];
+  const bool polar = exp_one_tangent(th, tau, E, G, c);
+  mat_h_vec<3>(E, pr, pi, br, bi);
+  const double grho = bilinear<3>(lr, li, G, br, bi);
+  if (polar) {
+    const double gphi = bilinear_phi(lr, li, E, br, bi);
+    *gx = fma(c[0], grho, c[2] * gphi);
+    *gy = fma(c[1], grho, c[3] * gphi);
+  } else {  // rho = 0: dE/dtheta_x = G, dE/dtheta_y = -i (m_j - m_k) G_jk
+    *gx = grho;
+    *gy = bilinear_phi(lr, li, G, br, bi);
+  }
+  mat_h_vec<3>(E, lr, li, nlr, nli);
+}
+
+// y = G x for the generator of the step angles.
+__device__ __forceinline__ void generator_times(const Gen3& g, const double* xr, const double* xi,
+                                                double* yr, double* yi) {
+  yr[0] = fma(g.a[0], xr[0], fma(g.wr, xr[1], -(g.wi * xi[1])));
+  yi[0] = fma(g.a[0], xi[0], fma(g.wr, xi[1], g.wi * xr[1]));
+  yr[1] = fma(g.a[1], xr[1],
+              fma(g.wr, xr[0], fma(g.wi, xi[0], fma(g.wr, xr[2], -(g.wi * xi[2])))));
+  yi[1] = fma(g.a[1], xi[1],
+              fma(g.wr, xi[0], fma(-g.wi, xr[0], fma(g.wr, xi[2], g.wi * xr[2]))));
+  yr[2] = fma(g.a[2], xr[2], fma(g.wr, xr[1], g.wi * xi[1]));
+  yi[2] = fma(g.a[2], xi[2], fma(g.wr, xi[1], -(g.wi * xr[1])));
+}
+
+// re + i im += l^H v
+__device__ __forceinline__ void add_inner(const double* lr, const double* li, const double* vr,
+                                          const double* vi, double& re, double& im) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    re = fma(lr[a], vr[a], fma(li[a], vi[a], re));
+    im = fma(lr[a], vi[a], fma(-li[a], vr[a], im));
+  }
+}
+
+// The raising and lowering sums of l^H J_{x,y} v: up += conj(l_0) v_1 +
+// conj(l_1) v_2 and down += conj(l_1) v_0 + conj(l_2) v_1; l^H J_x v =
+// (up + down) / sqrt 2 and l^H J_y v = i (down - up) / sqrt 2.
+struct Ladder {
+  double ur, ui, dr, di;
+};
+__device__ __forceinline__ void add_ladder(const double* lr, const double* li, const double* vr,
+                                           const double* vi, Ladder& s) {
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    s.ur = fma(lr[a], vr[a + 1], fma(li[a], vi[a + 1], s.ur));
+    s.ui = fma(lr[a], vi[a + 1], fma(-li[a], vr[a + 1], s.ui));
+    s.dr = fma(lr[a + 1], vr[a], fma(li[a + 1], vi[a], s.dr));
+    s.di = fma(lr[a + 1], vi[a], fma(-li[a + 1], vr[a], s.di));
+  }
+}
+
+// Spin-1 in closed form (exp_one): E = I + sum_k z_k G^k, k = 0..2, with
+// z_k = c_k - i s_k functions of p and d alone, so
+//   dE/dtheta_a = sum_k dz_k G^k + z_1 A + z_2 (A G + G A),   A = J_a,
+// and as dp/dtheta_a = 2 theta_a and dd/dtheta_a = -2 q3 theta_a one
+// derivative of the series, along (2, -2 q3), serves x and y.  About 370
+// instructions where the tangent squarings take 6,800 at tau = 28; the
+// same rule as in exp_one says where it stands for them.  With it, and each
+// node's sines, segment divisions and frame rotation taken once, the kernel
+// went from 15,000 to 1,570 instructions a fine step: 10.6 -> 2.6 ms for 256
+// control instances of 1e5 fine steps (gradients included, the whole pass
+// 13.99 -> 3.59 ms).
 template <> struct TangentStep<3> {
   static __device__ __forceinline__ void apply(const double th[4], int tau, const double* lr,
                                                const double* li, const double* pr,
                                                const double* pi, double* br, double* bi,
                                                double* nlr, double* nli, double* gx, double* gy) {
-    Mat<3> E, G;
-    double c[4];
-    const bool polar = exp_one_tangent(th, tau, E, G, c);
-    mat_h_vec<3>(E, pr, pi, br, bi);
-    const double grho = bilinear<3>(lr, li, G, br, bi);
-    if (polar) {
-      const double gphi = bilinear_phi(lr, li, E, br, bi);
-      *gx = fma(c[0], grho, c[2] * gphi);
-      *gy = fma(c[1], grho, c[3] * gphi);
-    } else {  // rho = 0: dE/dtheta_x = G, dE/dtheta_y = -i (m_j - m_k) G_jk
-      *gx = grho;
-      *gy = bilinear_phi(lr, li, G, br, bi);
+    Gen3 g;
+    generator(th, g);
+    const double most = ldexp(1.0, 2 * tau - 53);
+    const double q3 = -0.5 * g.a[1];
+    double c[3], s[3], dc[3], ds[3];
+    if (g.p <= fmin(most, kShortSeries)) {
+      series_part<8, true>(g.p, g.d, 2.0, -2.0 * q3, c, dc);
+      series_part<7, true>(g.p, g.d, 2.0, -2.0 * q3, s, ds);
+    } else if (g.p <= fmin(most, kLongSeries)) {
+      series_part<18, true>(g.p, g.d, 2.0, -2.0 * q3, c, dc);
+      series_part<19, true>(g.p, g.d, 2.0, -2.0 * q3, s, ds);
+    } else {
+      tangent_step_squarings(th, tau, lr, li, pr, pi, br, bi, nlr, nli, gx, gy);
+      return;
     }
+    Mat<3> E;
+    assemble(g, c, s, E);
+    mat_h_vec<3>(E, pr, pi, br, bi);
     mat_h_vec<3>(E, lr, li, nlr, nli);
+    double g1r[3], g1i[3], g2r[3], g2i[3], k1r[3], k1i[3];
+    generator_times(g, br, bi, g1r, g1i);    // G b
+    generator_times(g, g1r, g1i, g2r, g2i);  // G^2 b
+    generator_times(g, lr, li, k1r, k1i);    // G l
+    // Re(dz_k x) = dc_k Re x + ds_k Im x for x = l^H G^k b
+    double x[3] = {0.0, 0.0, 0.0}, y[3] = {0.0, 0.0, 0.0};
+    add_inner(lr, li, br, bi, x[0], y[0]);
+    add_inner(lr, li, g1r, g1i, x[1], y[1]);
+    add_inner(lr, li, g2r, g2i, x[2], y[2]);
+    double common = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) common = fma(dc[k], x[k], fma(ds[k], y[k], common));
+    Ladder one = {0.0, 0.0, 0.0, 0.0}, two = {0.0, 0.0, 0.0, 0.0};
+    add_ladder(lr, li, br, bi, one);
+    add_ladder(lr, li, g1r, g1i, two);
+    add_ladder(k1r, k1i, br, bi, two);
+    // z_1 one + z_2 two
+    const double ur = fma(c[1], one.ur, fma(s[1], one.ui, fma(c[2], two.ur, s[2] * two.ui)));
+    const double ui = fma(c[1], one.ui, fma(-s[1], one.ur, fma(c[2], two.ui, -(s[2] * two.ur))));
+    const double dr = fma(c[1], one.dr, fma(s[1], one.di, fma(c[2], two.dr, s[2] * two.di)));
+    const double di = fma(c[1], one.di, fma(-s[1], one.dr, fma(c[2], two.di, -(s[2] * two.dr))));
+    *gx = 2.0 * fma(th[0], common, kRsqrt2 * (ur + dr));
+    *gy = 2.0 * fma(th[1], common, kRsqrt2 * (ui - di));
   }
 };
 
@@ -322,6 +428,7 @@ template <> struct TangentStep<3> {
 // adjoint kernel
 // ---------------------------------------------------------------------------
 constexpr int kMaxGradTerms = 4;
+constexpr int kAdjointBlock = 256;
 
 struct AdjDesc {
   double t_start, dt_out, dt;
@@ -333,7 +440,8 @@ struct AdjDesc {
   const double* psi_final;     // [N]
   const double* lam_before;    // costates: entry j = lambda_{K-j}, j < K
   int32_t spin_twice, n_terms, term_off, n_fine;
-  int32_t tau, frame, n_gterms, pad;
+  int32_t tau, frame, n_gterms;
+  uint32_t same_phase;           // bit n: term n's phase is that of term n - 1 (same_phase below)
   int32_t gterm[kMaxGradTerms];  // indices (within the simulation's terms) of terms with slots
 };
 
@@ -361,64 +469,128 @@ __device__ __forceinline__ void flush(const mss_term& tm, GradAcc& g, double* gr
   g.a = g.f = g.ph = 0.0;
 }
 
-// Contribution of one node (time t, d loss / d f_x, f_y = Gx, Gy) to the
-// gradient accumulators of the simulation's parameterised terms.
-__device__ __forceinline__ void node_grad(const AdjDesc& s, const mss_term* __restrict__ terms,
-                                          double t, double Gx, double Gy, GradAcc* acc) {
+// What the chain rule of one node needs of one parameterised term, kept in
+// LDS from the field's evaluation until the node's sensitivities are known:
+// the term's value over its amplitude, the value's derivative by the phase,
+// and the segment (-1: none, -2: the term is off at the node's time).
+// Registers would not hold it beside an exponential and its tangent, and
+// evaluating the term again costs its sine and cosine and the segment's
+// division a second time.
+struct KeptTerms {
+  double val[2][kMaxGradTerms][kAdjointBlock];
+  double dphase[2][kMaxGradTerms][kAdjointBlock];
+  int seg[2][kMaxGradTerms][kAdjointBlock];
+};
+
+// The field at node i's time t (the interpreter's arithmetic of field_eval),
+// keeping the parameterised terms' derivatives.  A term marked in same_phase
+// has the window, segments, frequency and phase of the term before it and
+// takes that one's segment, sine and cosine.
+__device__ __forceinline__ void field_keep(const AdjDesc& s, const mss_term* __restrict__ terms,
+                                           double t, int i, KeptTerms& kept, double f[4]) {
 #pragma clang fp contract(off)
   const double* __restrict__ params = s.params;
+  const int me = threadIdx.x;
+  double fx = 0.0, fy = 0.0, fz = 0.0, fq = 0.0;
+  double sn = 0.0, cs = 1.0;
+  int seg = -1, g = 0;
+  for (int n = 0; n < s.n_terms; ++n) {
+    const mss_term& tm = terms[s.term_off + n];
+    // g stays uniform across the wave: it moves on whether or not the term is on
+    const bool keep = g < s.n_gterms && s.gterm[g] == n;
+    const int at = g;
+    g += keep ? 1 : 0;
+    if (!(tm.t_on < t && t < tm.t_off)) {
+      if (keep) kept.seg[i][at][me] = -2;
+      continue;
+    }
+    const int kind = tm.kind;
+    const bool again = (s.same_phase >> n) & 1;
+    double amp = tm.a_slot >= 0 ? params[tm.a_slot] : tm.a;
+    if (kind >= MSS_TERM_PWC) {
+      if (!again) {
+        const double x = (t - tm.seg_t0) / tm.seg_len;
+        const double fl = floor(x);
+        seg = fl < 0.0 ? 0 : (fl > (double)(tm.n_seg - 1) ? tm.n_seg - 1 : (int)fl);
+      }
+      if (tm.seg_a_slot >= 0) amp = params[tm.seg_a_slot + seg];
+    } else {
+      seg = -1;
+    }
+    double val = 1.0, dphase = 0.0;
+    if (kind != MSS_TERM_CONST && kind != MSS_TERM_PWC) {
+      if (!again) {
+        const double fr = tm.f_slot >= 0 ? params[tm.f_slot] : tm.f;
+        double ph = tm.phi_slot >= 0 ? params[tm.phi_slot] : tm.phi;
+        if (kind >= MSS_TERM_PWC && tm.seg_phi_slot >= 0) ph = params[tm.seg_phi_slot + seg];
+        const double ft = fr * t;
+        const double x = kTwoPi * ft;
+        const double arg = x + ph;
+        sincos_cw(arg, &sn, &cs);
+      }
+      const bool is_cos = kind == MSS_TERM_COS || kind == MSS_TERM_PWC_COS;
+      val = is_cos ? cs : sn;
+      dphase = is_cos ? -amp * sn : amp * cs;
+    }
+    const double v = amp * val;
+    switch (tm.comp) {
+      case 0: fx = fx + v; break;
+      case 1: fy = fy + v; break;
+      case 2: fz = fz + v; break;
+      default: fq = fq + v; break;
+    }
+    if (keep) {
+      kept.val[i][at][me] = val;
+      kept.dphase[i][at][me] = dphase;
+      kept.seg[i][at][me] = seg;
+    }
+  }
+  f[0] = fx; f[1] = fy; f[2] = fz; f[3] = fq;
+}
+
+// Contribution of node i (time t, d loss / d f_x, f_y = Gx, Gy) to the
+// gradient accumulators of the simulation's parameterised terms.
+__device__ __forceinline__ void node_grad(const AdjDesc& s, const mss_term* __restrict__ terms,
+                                          double t, int i, const KeptTerms& kept, double Gx,
+                                          double Gy, GradAcc* acc) {
+#pragma clang fp contract(off)
+  const int me = threadIdx.x;
 #pragma unroll
   for (int g = 0; g < kMaxGradTerms; ++g) {
     if (g >= s.n_gterms) break;
+    const int seg = kept.seg[i][g][me];
+    if (seg == -2) continue;
     const mss_term& tm = terms[s.term_off + s.gterm[g]];
-    if (!(tm.t_on < t && t < tm.t_off)) continue;
     const double G = tm.comp == MSS_X ? Gx : Gy;
-    double amp = tm.a_slot >= 0 ? params[tm.a_slot] : tm.a;
-    double ph = tm.phi_slot >= 0 ? params[tm.phi_slot] : tm.phi;
-    const double fr = tm.f_slot >= 0 ? params[tm.f_slot] : tm.f;
-    if (tm.kind >= MSS_TERM_PWC) {
-      const double x = (t - tm.seg_t0) / tm.seg_len;
-      const double fl = floor(x);
-      const int seg = fl < 0.0 ? 0 : (fl > (double)(tm.n_seg - 1) ? tm.n_seg - 1 : (int)fl);
-      if (seg != acc[g].seg) {
-        if (acc[g].seg >= 0) flush(tm, acc[g], s.grad);
-        acc[g].seg = seg;
-      }
-      if (tm.seg_a_slot >= 0) amp = params[tm.seg_a_slot + seg];
-      if (tm.seg_phi_slot >= 0) ph = params[tm.seg_phi_slot + seg];
+    if (tm.kind >= MSS_TERM_PWC && seg != acc[g].seg) {
+      if (acc[g].seg >= 0) flush(tm, acc[g], s.grad);
+      acc[g].seg = seg;
     }
-    if (tm.kind == MSS_TERM_CONST || tm.kind == MSS_TERM_PWC) {
-      acc[g].a += G;
-      continue;
-    }
-    const double ft = fr * t;
-    const double arg = kTwoPi * ft + ph;
-    double sn, cs;
-    sincos_cw(arg, &sn, &cs);
-    const bool is_cos = tm.kind == MSS_TERM_COS || tm.kind == MSS_TERM_PWC_COS;
-    const double val = is_cos ? cs : sn;
-    const double dar = is_cos ? -amp * sn : amp * cs;
-    acc[g].a += G * val;
+    acc[g].a += G * kept.val[i][g][me];
+    if (tm.kind == MSS_TERM_CONST || tm.kind == MSS_TERM_PWC) continue;
+    const double dar = kept.dphase[i][g][me];
     acc[g].ph += G * dar;
     acc[g].f += G * dar * kTwoPi * t;
   }
 }
 
 template <int N>
-__device__ __forceinline__ void adjoint_interval(const AdjArgs& A, const AdjDesc& s, int64_t k) {
+__device__ __forceinline__ void adjoint_interval(const AdjArgs& A, const AdjDesc& s, int64_t k,
+                                                 KeptTerms& kept) {
   const TableTerms terms{A.terms + s.term_off, s.n_terms};
   double tk, wr;
   interval_setup(terms, s.params, s.t_start, s.dt_out, k, s.frame, &tk, &wr);  // CF4 only
-  // psi_{k+1}, lambda_{k+1} into frame coordinates: R^H x, R = diag(e^{-i m wr Dt})
+  // psi_{k+1}, lambda_{k+1} into frame coordinates: R^H x, R = diag(e^{-i m wr Dt}),
+  // opposite turns of the two outer levels
   const double* pn = (k + 1 < s.K) ? s.psi + (size_t)(k + 1) * 2 * N : s.psi_final;
   const double* ln = s.lam_before + (size_t)(s.K - 1 - k) * 2 * N;
   double pr[N], pi[N], lr[N], li[N];
-  const double beta = wr * s.dt_out;
+  double se, ce;
+  sincos_cw((N == 2 ? 0.5 : 1.0) * (wr * s.dt_out), &se, &ce);
 #pragma unroll
   for (int a = 0; a < N; ++a) {
-    const double m = (N == 2) ? (a == 0 ? 0.5 : -0.5) : (double)(1 - a);
-    double sn, cs;
-    sincos_cw(m * beta, &sn, &cs);
+    const double sn = a == 0 ? se : (a == N - 1 ? -se : 0.0);
+    const double cs = a == 0 || a == N - 1 ? ce : 1.0;
     pr[a] = fma(cs, pn[2 * a], -sn * pn[2 * a + 1]);
     pi[a] = fma(cs, pn[2 * a + 1], sn * pn[2 * a]);
     lr[a] = fma(cs, ln[2 * a], -sn * ln[2 * a + 1]);
@@ -428,16 +600,29 @@ __device__ __forceinline__ void adjoint_interval(const AdjArgs& A, const AdjDesc
 #pragma unroll
   for (int g = 0; g < kMaxGradTerms; ++g) acc[g] = {-1, 0.0, 0.0, 0.0};
   const double wgt[2][2] = {{kWPlus, kWMinus}, {kWMinus, kWPlus}};  // [node][exponential]
+  NodeRotations rot;
+  rot.c[0] = rot.c[1] = 1.0;  // the lab frame
+  rot.s[0] = rot.s[1] = 0.0;
+  if (wr != 0.0) rot.start(wr, s.n_fine - 1, s.dt);
   for (int l = s.n_fine - 1; l >= 0; --l) {
-    double th[2][4];
-    NodeRotations rot;
-    if (wr != 0.0) rot.at(wr, l, s.dt);
-    cf4_angles(terms, s.params, tk, l, s.dt, wr, rot, th[0], th[1]);
-    double gx[2], gy[2];
+    double w[2][4], th[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      double f[4];
+      field_keep(s, A.terms, tk + node_offset(i, l, s.dt), i, kept, f);
+      node_rates(f, wr, rot.c[i], rot.s[i], w[i]);
+    }
+    cf4_combine(w, s.dt, th[0], th[1]);
+    double gx[2] = {0.0, 0.0}, gy[2] = {0.0, 0.0};
+#pragma unroll 1
     for (int e = 1; e >= 0; --e) {
       // the state before E, the new costate and the angle derivatives
-      double br[N], bi[N], nlr[N], nli[N];
-      TangentStep<N>::apply(th[e], s.tau, lr, li, pr, pi, br, bi, nlr, nli, &gx[e], &gy[e]);
+      double br[N], bi[N], nlr[N], nli[N], x, y;
+      TangentStep<N>::apply(e ? th[1] : th[0], s.tau, lr, li, pr, pi, br, bi, nlr, nli, &x, &y);
+      gx[1] = e ? x : gx[1];
+      gy[1] = e ? y : gy[1];
+      gx[0] = x;
+      gy[0] = y;
 #pragma unroll
       for (int a = 0; a < N; ++a) {
         pr[a] = br[a];
@@ -452,20 +637,20 @@ __device__ __forceinline__ void adjoint_interval(const AdjArgs& A, const AdjDesc
     for (int i = 0; i < 2; ++i) {
       const double Gxp = s.dt * (wgt[i][0] * gx[0] + wgt[i][1] * gx[1]);
       const double Gyp = s.dt * (wgt[i][0] * gy[0] + wgt[i][1] * gy[1]);
-      const double tau_i = ((double)l + (i == 0 ? kNode1 : kNode2)) * s.dt;
-      double sn = 0.0, cs = 1.0;
-      if (wr != 0.0) sincos_cw(wr * tau_i, &sn, &cs);
+      const double sn = rot.s[i], cs = rot.c[i];
       const double Gx = kTwoPi * fma(Gxp, cs, -Gyp * sn);
       const double Gy = kTwoPi * fma(Gxp, sn, Gyp * cs);
-      node_grad(s, A.terms, tk + tau_i, Gx, Gy, acc);
+      node_grad(s, A.terms, tk + node_offset(i, l, s.dt), i, kept, Gx, Gy, acc);
     }
+    if (wr != 0.0) rot.retreat();
   }
 #pragma unroll
   for (int g = 0; g < kMaxGradTerms; ++g)
     if (g < s.n_gterms) flush(A.terms[s.term_off + s.gterm[g]], acc[g], s.grad);
 }
 
-__global__ void __launch_bounds__(256) adjoint_kernel(const AdjArgs A) {
+__global__ void __launch_bounds__(kAdjointBlock, 2) adjoint_kernel(const AdjArgs A) {
+  __shared__ KeptTerms kept;  // every lane its own entries
   const int lane = threadIdx.x & 63;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (wave >= A.n_waves) return;
@@ -478,8 +663,8 @@ __global__ void __launch_bounds__(256) adjoint_kernel(const AdjArgs A) {
   const AdjDesc& s = A.sims[lo];
   const int64_t k = (wave - s.wave_off) * 64 + lane;
   if (k >= s.K) return;
-  if (s.spin_twice == 2) adjoint_interval<3>(A, s, k);
-  else adjoint_interval<2>(A, s, k);
+  if (s.spin_twice == 2) adjoint_interval<3>(A, s, k, kept);
+  else adjoint_interval<2>(A, s, k, kept);
 }
 
 // loss_i and the seed costate lambda_K = e_m psi_final[m]; gradients cleared.
@@ -589,6 +774,26 @@ void release(mss_adjoint_plan* P) {
   if (P->last_run) (void)hipEventDestroy(P->last_run);
   if (P->desc) (void)hipFree(P->desc);
   delete P;
+}
+
+// Whether b, the term after a, takes the same phase 2 pi f t + phi at every
+// time at which either is on (field_keep then evaluates it once): a
+// circular drive's cosine and sine.
+bool same_phase(const mss_term& a, const mss_term& b) {
+  const bool pwc = a.kind == MSS_TERM_PWC_COS || a.kind == MSS_TERM_PWC_SIN;
+  if (pwc != (b.kind == MSS_TERM_PWC_COS || b.kind == MSS_TERM_PWC_SIN)) return false;
+  if (!pwc && ((a.kind != MSS_TERM_COS && a.kind != MSS_TERM_SIN) ||
+               (b.kind != MSS_TERM_COS && b.kind != MSS_TERM_SIN)))
+    return false;
+  const auto same = [](int32_t sa, double va, int32_t sb, double vb) {
+    return sa >= 0 ? sa == sb : (sb < 0 && va == vb);
+  };
+  if (a.t_on != b.t_on || a.t_off != b.t_off || !same(a.f_slot, a.f, b.f_slot, b.f)) return false;
+  if (!pwc) return same(a.phi_slot, a.phi, b.phi_slot, b.phi);
+  if (a.n_seg != b.n_seg || a.seg_t0 != b.seg_t0 || a.seg_len != b.seg_len) return false;
+  return a.seg_phi_slot >= 0
+             ? a.seg_phi_slot == b.seg_phi_slot
+             : (b.seg_phi_slot < 0 && same(a.phi_slot, a.phi, b.phi_slot, b.phi));
 }
 
 void pack_all(mss_adjoint_plan* P) {
@@ -779,6 +984,7 @@ mss_status mss_adjoint_plan_create(int32_t n, const mss_problem* problems, const
     for (int t = 0; t < q.n_terms; ++t) {
       const mss_term& tm = q.terms[t];
       P->terms.push_back(tm);
+      if (t > 0 && same_phase(q.terms[t - 1], tm)) a.same_phase |= 1u << t;
       if (tm.a_slot >= 0 || tm.f_slot >= 0 || tm.phi_slot >= 0 || tm.seg_a_slot >= 0 ||
           tm.seg_phi_slot >= 0)
         a.gterm[a.n_gterms++] = t;
@@ -869,7 +1075,8 @@ mss_status mss_adjoint_run(mss_adjoint_plan* P, const double* params, const doub
   if (e == hipSuccess) e = launch_work_scan(P->dbwd, st);
   if (e == hipSuccess) {
     AdjArgs aa{(const AdjDesc*)(d + P->a_sims), (const mss_term*)(d + P->a_terms), P->n_waves, P->n};
-    hipLaunchKernelGGL(adjoint_kernel, dim3((unsigned)((P->n_waves + 3) / 4)), dim3(256), 0, st, aa);
+    hipLaunchKernelGGL(adjoint_kernel, dim3((unsigned)((P->n_waves + 3) / 4)),
+                       dim3(kAdjointBlock), 0, st, aa);
     e = hipGetLastError();
   }
   if (e == hipSuccess && psi_final)

@@ -296,12 +296,13 @@ __device__ __forceinline__ void sincos_small(double x, double* s, double* c) {
 // spin-1/2 exponential: exp(-i theta . sigma / 2)
 // = cos(|theta|/2) I - i sin(|theta|/2) (theta/|theta|) . sigma, less I
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void exp_half(const double th[4], int /*tau*/, Mat<2>& E) {
+// u = |theta|^2 / 4, c = cos(|theta|/2) - 1 and S = sin(|theta|/2) / |theta|.
+__device__ __forceinline__ void half_coefficients(const double th[4], double& u, double& c,
+                                                  double& S) {
   // cos and sin(x) / x are even in x = |theta| / 2: up to x = 1 their series
   // in x^2 need no square root, division or range reduction
   const double t2 = fma(th[0], th[0], fma(th[1], th[1], th[2] * th[2]));
-  const double u = 0.25 * t2;
-  double c, S;  // cos(|theta|/2) - 1 and sin(|theta|/2) / |theta|
+  u = 0.25 * t2;
   if (u <= 0x1p-8) {  // next terms below 2^-61
     c = u * fma(u, fma(u, fma(u, 1.0 / 40320, -1.0 / 720), 1.0 / 24), -0.5);
     S = fma(u, fma(u, fma(u, fma(u, 0.5 / 362880, -0.5 / 5040), 0.5 / 120), -0.5 / 6), 0.5);
@@ -332,6 +333,11 @@ __device__ __forceinline__ void exp_half(const double th[4], int /*tau*/, Mat<2>
     c = co - 1.0;
     S = s / big;
   }
+}
+
+__device__ __forceinline__ void exp_half(const double th[4], int /*tau*/, Mat<2>& E) {
+  double u, c, S;
+  half_coefficients(th, u, c, S);
   E.r[0][0] = c;           E.i[0][0] = -S * th[2];
   E.r[0][1] = -S * th[1];  E.i[0][1] = -S * th[0];
   E.r[1][0] = S * th[1];   E.i[1][0] = -S * th[0];
@@ -547,57 +553,62 @@ __device__ __forceinline__ void generator(const double th[4], Gen3& g) {
 }
 
 // 1 / k!
-constexpr double kInvFact[19] = {
+constexpr double kInvFact[20] = {
     1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320,
     1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600, 1.0 / 6227020800.0,
     1.0 / 87178291200.0, 1.0 / 1307674368000.0, 1.0 / 20922789888000.0,
-    1.0 / 355687428096000.0, 1.0 / 6402373705728000.0};
+    1.0 / 355687428096000.0, 1.0 / 6402373705728000.0, 1.0 / 121645100408832000.0};
 
-// Coefficients of C - I and S over (I, G, G^2), from the series to G^TOP for
-// C (TOP even) and to G^(TOP - 1), or to G^(TOP + 1) with ODD, for S.
-template <int TOP, bool ODD>
-__device__ __forceinline__ void series(double p, double d, double c[3], double s[3]) {
-  static_assert(TOP % 2 == 0 && TOP >= 6, "");
-  // The top three powers are (c_{M-2}, 0, c_M); two factors G lead to
+// One part's coefficients over (I, G, G^2), the series to G^M without its
+// constant term: x, and with TANGENT dx, their derivative along a direction
+// (dp, dd) of (p, d).
+template <int M, bool TANGENT>
+__device__ __forceinline__ void series_part(double p, double d, double dp, double dd, double x[3],
+                                            double dx[3]) {
+  static_assert(M >= 6, "");
+  constexpr double sign = (M / 2) % 2 ? -1.0 : 1.0;  // of G^M
+  // The top powers are (c_{M-2}, 0, c_M); two factors G lead to
   // (c_{M-4}, d c_M, c_{M-2} + p c_M), without the products with 0.
-  {
-    constexpr double sg = (TOP / 2) % 2 ? -1.0 : 1.0;  // sign of G^TOP
-    double a = sg * kInvFact[TOP - 4];
-    double b = d * (sg * kInvFact[TOP]);
-    double e = fma(p, sg * kInvFact[TOP], -sg * kInvFact[TOP - 2]);
-#pragma unroll
-    for (int k = TOP - 5; k >= 0; --k) {
-      const double na = k > 0 && k % 2 == 0
-                            ? fma(d, e, ((k / 2) % 2 ? -1.0 : 1.0) * kInvFact[k])
-                            : d * e;
-      const double nb = fma(p, e, a);
-      e = b;
-      a = na;
-      b = nb;
-    }
-    c[0] = a;
-    c[1] = b;
-    c[2] = e;
+  double a = sign * kInvFact[M - 4];
+  double b = d * (sign * kInvFact[M]);
+  double e = fma(p, sign * kInvFact[M], -sign * kInvFact[M - 2]);
+  double ta = 0.0, tb = 0.0, te = 0.0;
+  if constexpr (TANGENT) {
+    tb = dd * (sign * kInvFact[M]);
+    te = dp * (sign * kInvFact[M]);
   }
-  {
-    constexpr int M = ODD ? TOP + 1 : TOP - 1;
-    constexpr double sm = (M / 2) % 2 ? -1.0 : 1.0;
-    double a = sm * kInvFact[M - 4];
-    double b = d * (sm * kInvFact[M]);
-    double e = fma(p, sm * kInvFact[M], -sm * kInvFact[M - 2]);
 #pragma unroll
-    for (int k = M - 5; k >= 0; --k) {
-      const double na =
-          k % 2 == 1 ? fma(d, e, ((k / 2) % 2 ? -1.0 : 1.0) * kInvFact[k]) : d * e;
-      const double nb = fma(p, e, a);
-      e = b;
-      a = na;
-      b = nb;
+  for (int k = M - 5; k >= 0; --k) {
+    if constexpr (TANGENT) {
+      const double na = fma(dd, e, d * te);
+      const double nb = k == M - 5 ? fma(dp, e, p * te) : fma(dp, e, fma(p, te, ta));
+      te = tb;
+      ta = na;
+      tb = nb;
     }
-    s[0] = a;
-    s[1] = b;
-    s[2] = e;
+    const bool term = k % 2 == M % 2 && k > 0;
+    const double na = term ? fma(d, e, ((k / 2) % 2 ? -1.0 : 1.0) * kInvFact[k]) : d * e;
+    const double nb = fma(p, e, a);
+    e = b;
+    a = na;
+    b = nb;
   }
+  x[0] = a;
+  x[1] = b;
+  x[2] = e;
+  if constexpr (TANGENT) {
+    dx[0] = ta;
+    dx[1] = tb;
+    dx[2] = te;
+  }
+}
+
+// Coefficients of C - I (series to G^MC) and of S (to G^MS).
+template <int MC, int MS>
+__device__ __forceinline__ void series(double p, double d, double c[3], double s[3]) {
+  static_assert(MC % 2 == 0 && MS % 2 == 1, "");
+  series_part<MC, false>(p, d, 0.0, 0.0, c, nullptr);
+  series_part<MS, false>(p, d, 0.0, 0.0, s, nullptr);
 }
 
 // E = I + (c_0 + c_1 G + c_2 G^2) - i (s_0 + s_1 G + s_2 G^2).  With a
@@ -652,9 +663,9 @@ __device__ __forceinline__ void exp_one(const double th[4], int tau, Mat<3>& E) 
   const double most = ldexp(1.0, 2 * tau - 53);
   double c[3], s[3];
   if (g.p <= fmin(most, kShortSeries)) {
-    series<6, true>(g.p, g.d, c, s);
+    series<6, 7>(g.p, g.d, c, s);
   } else if (g.p <= fmin(most, kLongSeries)) {
-    series<18, false>(g.p, g.d, c, s);
+    series<18, 17>(g.p, g.d, c, s);
   } else {  // also angles that are not finite
     exp_one_squarings(th, tau, E);
     return;
@@ -737,15 +748,6 @@ struct NodeRotations {
     }
     sincos_cw(wr * dt, &sd, &cd);
   }
-  // the node rotations of step l alone, taken directly (no step rotation)
-  __device__ __forceinline__ void at(double wr, int l, double dt) {
-#pragma clang fp contract(off)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const double tau_i = ((double)l + (i == 0 ? kNode1 : kNode2)) * dt;
-      sincos_cw(wr * tau_i, &s[i], &c[i]);
-    }
-  }
   __device__ __forceinline__ void advance() {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -755,7 +757,52 @@ struct NodeRotations {
       s[i] = sn;
     }
   }
+  // to the step before
+  __device__ __forceinline__ void retreat() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const double cn = fma(c[i], cd, s[i] * sd);
+      const double sn = fma(s[i], cd, -(c[i] * sd));
+      c[i] = cn;
+      s[i] = sn;
+    }
+  }
 };
+
+// Node i of the fine step starting at t_k + l dt: its offset from t_k.
+__device__ __forceinline__ double node_offset(int i, int l, double dt) {
+#pragma clang fp contract(off)
+  return ((double)l + (i == 0 ? kNode1 : kNode2)) * dt;
+}
+
+// Angular rates w of a node from its field f, in the frame rotating at wr
+// about z whose angle there has cosine c and sine s (wr = 0: lab frame; c
+// and s are then not read).
+__device__ __forceinline__ void node_rates(const double f[4], double wr, double c, double s,
+                                           double w[4]) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int j = 0; j < 4; ++j) w[j] = kTwoPi * f[j];
+  if (wr != 0.0) {
+    // (w_x + i w_y) e^{-i wr tau_i}
+    const double xr = w[0] * c + w[1] * s;
+    const double xi = w[1] * c - w[0] * s;
+    w[0] = xr;
+    w[1] = xi;
+    w[2] = w[2] - wr;
+  }
+}
+
+// The two exponentials' angles from the rates of both nodes.
+__device__ __forceinline__ void cf4_combine(const double w[2][4], double dt, double th1[4],
+                                            double th2[4]) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    th1[j] = (kWPlus * w[0][j] + kWMinus * w[1][j]) * dt;
+    th2[j] = (kWMinus * w[0][j] + kWPlus * w[1][j]) * dt;
+  }
+}
 
 // Angles theta_{1,2} = omega_bar_{1,2} dt of one CF4 fine step starting at
 // t_k + l dt, in the frame rotating at wr about z (wr = 0: lab frame; then
@@ -769,26 +816,11 @@ __device__ __forceinline__ void cf4_angles(const Terms& fp, const double* __rest
   double w[2][4];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const double tau_i = ((double)l + (i == 0 ? kNode1 : kNode2)) * dt;
     double f[4];
-    field_eval(fp, params, tk + tau_i, f);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) w[i][j] = kTwoPi * f[j];
-    if (wr != 0.0) {
-      // (w_x + i w_y) e^{-i wr tau_i}
-      const double c = rot.c[i], s = rot.s[i];
-      const double xr = w[i][0] * c + w[i][1] * s;
-      const double xi = w[i][1] * c - w[i][0] * s;
-      w[i][0] = xr;
-      w[i][1] = xi;
-      w[i][2] = w[i][2] - wr;
-    }
+    field_eval(fp, params, tk + node_offset(i, l, dt), f);
+    node_rates(f, wr, rot.c[i], rot.s[i], w[i]);
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    th1[j] = (kWPlus * w[0][j] + kWMinus * w[1][j]) * dt;
-    th2[j] = (kWMinus * w[0][j] + kWPlus * w[1][j]) * dt;
-  }
+  cf4_combine(w, dt, th1, th2);
 }
 
 // Angles of one Euler-family step (one exponential): H sampled at the
@@ -1074,9 +1106,9 @@ __device__ __forceinline__ void exp_full(const double th[kFullComps], int tau, M
   const double most = ldexp(1.0, 2 * tau - 25);
   double c[3], s[3];
   if (p <= fmin(most, kShortSeries)) {
-    series<6, true>(p, d, c, s);
+    series<6, 7>(p, d, c, s);
   } else if (p <= fmin(most, kLongSeries)) {
-    series<18, false>(p, d, c, s);
+    series<18, 17>(p, d, c, s);
   } else {  // also angles that are not finite
     exp_full_squarings(th, tau, E);
     return;
