@@ -482,7 +482,7 @@ struct KeptTerms {
   int seg[2][kMaxGradTerms][kAdjointBlock];
 };
 
-// The field at node i's time t (the interpreter's arithmetic of field_eval),
+// The field at node i's time t (the interpreter's arithmetic of field_at),
 // keeping the parameterised terms' derivatives.  A term marked in same_phase
 // has the window, segments, frequency and phase of the term before it and
 // takes that one's segment, sine and cosine.
@@ -577,9 +577,11 @@ __device__ __forceinline__ void node_grad(const AdjDesc& s, const mss_term* __re
 template <int N>
 __device__ __forceinline__ void adjoint_interval(const AdjArgs& A, const AdjDesc& s, int64_t k,
                                                  KeptTerms& kept) {
-  const TableTerms terms{A.terms + s.term_off, s.n_terms};
+  // the list as it stands: no part of it is set apart as constant
+  const TableTerms terms{A.terms + s.term_off, s.n_terms, s.n_terms};
+  const double none[4] = {0.0, 0.0, 0.0, 0.0};
   double tk, wr;
-  interval_setup(terms, s.params, s.t_start, s.dt_out, k, s.frame, &tk, &wr);  // CF4 only
+  interval_setup(terms, s.params, none, s.t_start, s.dt_out, k, s.frame, &tk, &wr);  // CF4 only
   // psi_{k+1}, lambda_{k+1} into frame coordinates: R^H x, R = diag(e^{-i m wr Dt}),
   // opposite turns of the two outer levels
   const double* pn = (k + 1 < s.K) ? s.psi + (size_t)(k + 1) * 2 * N : s.psi_final;

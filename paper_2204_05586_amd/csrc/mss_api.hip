@@ -278,6 +278,21 @@ void api_plan_lane_segments(IntervalGrid& g, int S0, bool given, int64_t slots) 
   g.seg_w0[1] = full;
 }
 
+int program_order(const mss_term* terms, int n, mss_term* out) {
+  unsigned varying = 0;  // components
+  for (int i = 0; i < n; ++i)
+    if (terms[i].kind != MSS_TERM_CONST || terms[i].t_on != -INFINITY ||
+        terms[i].t_off != INFINITY)
+      varying |= 1u << terms[i].comp;
+  int k = 0;
+  for (int i = 0; i < n; ++i)
+    if ((varying >> terms[i].comp) & 1) out[k++] = terms[i];
+  const int n_varying = k;
+  for (int i = 0; i < n; ++i)
+    if (!((varying >> terms[i].comp) & 1)) out[k++] = terms[i];
+  return n_varying;
+}
+
 int64_t api_grid_waves(const IntervalGrid& g) {
   const int j = g.n_seg - 1;
   const int64_t per = 64 >> g.seg_sl[j];
@@ -413,7 +428,7 @@ mss_status mss_integrate(const mss_problem* p, const double* params, double* U, 
   IntegrateArgs a;
   memset(&a, 0, sizeof a);
   a.fp.n_terms = p->n_terms;
-  for (int i = 0; i < p->n_terms; ++i) a.fp.t[i] = p->terms[i];
+  a.fp.n_varying = program_order(p->terms, p->n_terms, a.fp.t);
   a.g.params = params;
   a.g.U = U;
   a.g.time = time;

@@ -24,9 +24,12 @@ constexpr double kTwoPi = 0x1.921fb54442d18p+2;
 constexpr double kRsqrt2 = 0x1.6a09e667f3bccp-1;
 
 // Field program as a kernel argument (scalar-loaded, uniform across a wave).
+// The first n_varying terms are those of components that depend on time, in
+// list order; the others belong to components all of whose terms are
+// constant and always on (program_order).
 struct FieldProgram {
   int32_t n_terms;
-  int32_t pad;
+  int32_t n_varying;
   mss_term t[MSS_MAX_TERMS];
 };
 
@@ -47,13 +50,15 @@ struct ArgTerms {
   static constexpr bool kFullBasis = true;  // field programs may use all eight components
   const FieldProgram& fp;
   __device__ __forceinline__ int size() const { return fp.n_terms; }
+  __device__ __forceinline__ int varying() const { return fp.n_varying; }
   __device__ __forceinline__ const mss_term& operator[](int i) const { return fp.t[i]; }
 };
 struct TableTerms {
   static constexpr bool kFullBasis = true;
   const mss_term* __restrict__ t;
-  int n;
+  int n, n_varying;
   __device__ __forceinline__ int size() const { return n; }
+  __device__ __forceinline__ int varying() const { return n_varying; }
   __device__ __forceinline__ const mss_term& operator[](int i) const { return t[i]; }
 };
 
@@ -244,11 +249,11 @@ constexpr double kPio2_1 = 0x1.921fb54400000p+0;
 constexpr double kPio2_2 = 0x1.0b4611a600000p-34;
 constexpr double kPio2_3 = 0x1.3198a2e037073p-69;
 
-__device__ __forceinline__ void sincos_cw(double x, double* s, double* c) {
-  if (!(fabs(x) < 0x1.8p+20)) {
-    sincos(x, s, c);
-    return;
-  }
+// |x| < 1.5 * 2^20 (NaN: no)
+__device__ __forceinline__ bool sincos_in_range(double x) { return fabs(x) < 0x1.8p+20; }
+
+// The reduction and series for an x in range.
+__device__ __forceinline__ void sincos_reduced(double x, double* s, double* c) {
   const double k = rint(x * kTwoOverPi);
   double r = fma(-k, kPio2_1, x);
   r = fma(-k, kPio2_2, r);
@@ -277,6 +282,26 @@ __device__ __forceinline__ void sincos_cw(double x, double* s, double* c) {
   const double c1 = (q & 1) ? sn : cn;
   *s = (q & 2) ? -s1 : s1;
   *c = ((q + 1) & 2) ? -c1 : c1;
+}
+
+__device__ __forceinline__ void sincos_cw(double x, double* s, double* c) {
+  if (sincos_in_range(x)) sincos_reduced(x, s, c);
+  else sincos(x, s, c);
+}
+
+// Of M arguments at once: with all in range there is one branch and the M
+// chains of dependent operations run side by side.
+template <int M>
+__device__ __forceinline__ void sincos_cw(const double (&x)[M], double (&s)[M], double (&c)[M]) {
+  bool all = true;
+#pragma unroll
+  for (int i = 0; i < M; ++i) all = all && sincos_in_range(x[i]);
+  if (all) {
+#pragma unroll
+    for (int i = 0; i < M; ++i) sincos_reduced(x[i], &s[i], &c[i]);
+  } else {
+    for (int i = 0; i < M; ++i) sincos_cw(x[i], &s[i], &c[i]);
+  }
 }
 
 // Tiny angles inside the exponentiators: below 2^-10 the Taylor series to
@@ -691,45 +716,99 @@ template <> struct Exponentiator<3> {
 // exactly as the plain definition t_k = t_start + k Dt,
 // tau_i = (l + c_i) dt, phase = 2 pi (f t) + phi prescribes.
 // ---------------------------------------------------------------------------
-template <class Terms>
-__device__ __forceinline__ void field_eval(const Terms& fp, const double* __restrict__ params,
-                                           double t, double f[4]) {
+// The field over C components (4, or 8 in the full basis) comes in two parts.
+// field_constant: the components whose terms are all constant, once per
+// interval; the others 0.
+template <int C, class Terms>
+__device__ __forceinline__ void field_constant(const Terms& fp, const double* __restrict__ params,
+                                               double (&fc)[C]) {
 #pragma clang fp contract(off)
-  double fx = 0.0, fy = 0.0, fz = 0.0, fq = 0.0;
+#pragma unroll
+  for (int j = 0; j < C; ++j) fc[j] = 0.0;
   const int nt = fp.size();
+  for (int n = fp.varying(); n < nt; ++n) {
+    const mss_term& tm = fp[n];
+    const double v = tm.a_slot >= 0 ? params[tm.a_slot] : tm.a;
+    const int comp = tm.comp;
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+      if (comp == j) fc[j] = fc[j] + v;  // uniform across the wave
+  }
+}
+
+// field_at: the whole field at M times, the constant part given: one walk
+// over the varying terms for all of them (each term is read once, and the M
+// chains of dependent operations run side by side).  only >= 0: no other
+// component is wanted.  Terms of one component are summed in list order.
+// What bounds the interpreter is the latency of its scalar loads and
+// branches between the sines: 1e6 spin-1 intervals of 10 fine steps, sensing
+// drive, took 391 us with a walk over all terms at every node and take 261
+// (203 with the field compiled in); 3e5 spin-1/2 intervals of 20, 103 and 76.
+template <int C, int M, class Terms>
+__device__ __forceinline__ void field_at(const Terms& fp, const double* __restrict__ params,
+                                         const double (&fc)[C], const double (&t)[M],
+                                         double (&f)[M][C], int only = -1) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+#pragma unroll
+    for (int j = 0; j < C; ++j) f[i][j] = fc[j];
+  const int nt = fp.varying();
   for (int n = 0; n < nt; ++n) {
     const mss_term& tm = fp[n];
-    if (!(tm.t_on < t && t < tm.t_off)) continue;
-    double amp = tm.a_slot >= 0 ? params[tm.a_slot] : tm.a;
-    const double fr = tm.f_slot >= 0 ? params[tm.f_slot] : tm.f;
-    double ph = tm.phi_slot >= 0 ? params[tm.phi_slot] : tm.phi;
-    const int kind = tm.kind;
+    const int comp = tm.comp, kind = tm.kind;
+    if (only >= 0 && comp != only) continue;
+    const double t_on = tm.t_on, t_off = tm.t_off;
+    bool on[M], any = false;
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      on[i] = t_on < t[i] && t[i] < t_off;
+      any = any || on[i];
+    }
+    if (!any) continue;
+    const double a = tm.a_slot >= 0 ? params[tm.a_slot] : tm.a;
+    double amp[M], v[M];
+#pragma unroll
+    for (int i = 0; i < M; ++i) amp[i] = a;
+    int seg[M];
     if (kind >= MSS_TERM_PWC) {
-      const double x = (t - tm.seg_t0) / tm.seg_len;
-      const double fl = floor(x);
-      int s = fl < 0.0 ? 0 : (fl > (double)(tm.n_seg - 1) ? tm.n_seg - 1 : (int)fl);
-      if (tm.seg_a_slot >= 0) amp = params[tm.seg_a_slot + s];
-      if (tm.seg_phi_slot >= 0) ph = params[tm.seg_phi_slot + s];
+      const double t0 = tm.seg_t0, len = tm.seg_len;
+      const int last = tm.n_seg - 1;
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        const double x = (t[i] - t0) / len;
+        const double fl = floor(x);
+        seg[i] = fl < 0.0 ? 0 : (fl > (double)last ? last : (int)fl);
+        if (tm.seg_a_slot >= 0) amp[i] = params[tm.seg_a_slot + seg[i]];
+      }
     }
-    double v;
     if (kind == MSS_TERM_CONST || kind == MSS_TERM_PWC) {
-      v = amp;
+#pragma unroll
+      for (int i = 0; i < M; ++i) v[i] = amp[i];
     } else {
-      const double ft = fr * t;
-      const double x = kTwoPi * ft;
-      const double arg = x + ph;
-      double sn, cs;
-      sincos_cw(arg, &sn, &cs);
-      v = amp * ((kind == MSS_TERM_COS || kind == MSS_TERM_PWC_COS) ? cs : sn);
+      const double fr = tm.f_slot >= 0 ? params[tm.f_slot] : tm.f;
+      const double phi = tm.phi_slot >= 0 ? params[tm.phi_slot] : tm.phi;
+      double arg[M], sn[M], cs[M];
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        double ph = phi;
+        if (kind >= MSS_TERM_PWC && tm.seg_phi_slot >= 0) ph = params[tm.seg_phi_slot + seg[i]];
+        const double ft = fr * t[i];
+        const double x = kTwoPi * ft;
+        arg[i] = x + ph;
+      }
+      sincos_cw(arg, sn, cs);
+      const bool is_cos = kind == MSS_TERM_COS || kind == MSS_TERM_PWC_COS;
+#pragma unroll
+      for (int i = 0; i < M; ++i) v[i] = amp[i] * (is_cos ? cs[i] : sn[i]);
     }
-    switch (tm.comp) {
-      case 0: fx = fx + v; break;
-      case 1: fy = fy + v; break;
-      case 2: fz = fz + v; break;
-      default: fq = fq + v; break;
-    }
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+      if (comp == j) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) f[i][j] = on[i] ? f[i][j] + v[i] : f[i][j];
+      }
   }
-  f[0] = fx; f[1] = fy; f[2] = fz; f[3] = fq;
 }
 
 // Frame rotations of the two CF4 nodes of a run of fine steps: cos and sin
@@ -741,12 +820,16 @@ struct NodeRotations {
   double cd, sd;      // cos, sin of wr dt
   __device__ __forceinline__ void start(double wr, int l, double dt) {
 #pragma clang fp contract(off)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const double tau_i = ((double)l + (i == 0 ? kNode1 : kNode2)) * dt;
-      sincos_cw(wr * tau_i, &s[i], &c[i]);
-    }
-    sincos_cw(wr * dt, &sd, &cd);
+    const double x[3] = {wr * (((double)l + kNode1) * dt), wr * (((double)l + kNode2) * dt),
+                         wr * dt};
+    double sn[3], cs[3];
+    sincos_cw(x, sn, cs);
+    s[0] = sn[0];
+    s[1] = sn[1];
+    sd = sn[2];
+    c[0] = cs[0];
+    c[1] = cs[1];
+    cd = cs[2];
   }
   __device__ __forceinline__ void advance() {
 #pragma unroll
@@ -809,17 +892,15 @@ __device__ __forceinline__ void cf4_combine(const double w[2][4], double dt, dou
 // rot is not read).
 template <class Terms>
 __device__ __forceinline__ void cf4_angles(const Terms& fp, const double* __restrict__ params,
-                                           double tk, int l, double dt, double wr,
-                                           const NodeRotations& rot, double th1[4],
+                                           const double (&fc)[4], double tk, int l, double dt,
+                                           double wr, const NodeRotations& rot, double th1[4],
                                            double th2[4]) {
 #pragma clang fp contract(off)
-  double w[2][4];
+  const double t[2] = {tk + node_offset(0, l, dt), tk + node_offset(1, l, dt)};
+  double f[2][4], w[2][4];
+  field_at(fp, params, fc, t, f);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    double f[4];
-    field_eval(fp, params, tk + node_offset(i, l, dt), f);
-    node_rates(f, wr, rot.c[i], rot.s[i], w[i]);
-  }
+  for (int i = 0; i < 2; ++i) node_rates(f[i], wr, rot.c[i], rot.s[i], w[i]);
   cf4_combine(w, dt, th1, th2);
 }
 
@@ -827,44 +908,39 @@ __device__ __forceinline__ void cf4_angles(const Terms& fp, const double* __rest
 // midpoint (method 1) or averaged over both ends of the step (method 2).
 template <class Terms>
 __device__ __forceinline__ void euler_angles(const Terms& fp, const double* __restrict__ params,
-                                             double tk, int l, double dt, double wr, int method,
-                                             double th[4]) {
+                                             const double (&fc)[4], double tk, int l, double dt,
+                                             double wr, int method, double th[4]) {
 #pragma clang fp contract(off)
   const int nn = method == 1 ? 1 : 2;
   double w[2][4];
   for (int i = 0; i < nn; ++i) {
     const double c = method == 1 ? 0.5 : (i == 0 ? 0.0 : 1.0);
     const double tau_i = ((double)l + c) * dt;
-    double f[4];
-    field_eval(fp, params, tk + tau_i, f);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) w[i][j] = kTwoPi * f[j];
-    if (wr != 0.0) {
-      double s, cs;
-      sincos_cw(wr * tau_i, &s, &cs);
-      const double xr = w[i][0] * cs + w[i][1] * s;
-      const double xi = w[i][1] * cs - w[i][0] * s;
-      w[i][0] = xr;
-      w[i][1] = xi;
-      w[i][2] = w[i][2] - wr;
-    }
+    const double t[1] = {tk + tau_i};
+    double f[1][4], s = 0.0, cs = 1.0;
+    field_at(fp, params, fc, t, f);
+    if (wr != 0.0) sincos_cw(wr * tau_i, &s, &cs);
+    node_rates(f[0], wr, cs, s, w[i]);
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) th[j] = (method == 1 ? w[0][j] : (w[0][j] + w[1][j]) / 2.0) * dt;
 }
 
-// Start time of interval k and the frame rate omega_r = 2 pi f_z(t_k + Dt/2).
-template <class Terms>
+// Start time of interval k and the frame rate omega_r = 2 pi f_z(t_k + Dt/2)
+// (fc: the constant part of the field).
+template <int C, class Terms>
 __device__ __forceinline__ void interval_setup(const Terms& fp, const double* __restrict__ params,
-                                               double t_start, double Dt, int64_t k, int frame,
-                                               double* tk_out, double* wr_out) {
+                                               const double (&fc)[C], double t_start, double Dt,
+                                               int64_t k, int frame, double* tk_out,
+                                               double* wr_out) {
 #pragma clang fp contract(off)
   const double tk = t_start + (double)k * Dt;
   double wr = 0.0;
   if (frame) {
-    double f[4];
-    field_eval(fp, params, tk + Dt / 2.0, f);
-    wr = kTwoPi * f[2];
+    const double t[1] = {tk + Dt / 2.0};
+    double f[1][C];
+    field_at(fp, params, fc, t, f, MSS_Z);
+    wr = kTwoPi * f[0][MSS_Z];
   }
   *tk_out = tk;
   *wr_out = wr;
@@ -900,53 +976,6 @@ __device__ __forceinline__ void exit_frame(double wr, double Dt, Mat<N>& U) {
 // ---------------------------------------------------------------------------
 constexpr int kFullComps = 8;
 
-// The field at time t over the eight components, terms summed in list order
-// (the interpreter's arithmetic of field_eval).
-template <class Terms>
-__device__ __forceinline__ void field_eval_full(const Terms& fp, const double* __restrict__ params,
-                                                double t, double f[kFullComps]) {
-#pragma clang fp contract(off)
-#pragma unroll
-  for (int j = 0; j < kFullComps; ++j) f[j] = 0.0;
-  const int nt = fp.size();
-  for (int n = 0; n < nt; ++n) {
-    const mss_term& tm = fp[n];
-    if (!(tm.t_on < t && t < tm.t_off)) continue;
-    double amp = tm.a_slot >= 0 ? params[tm.a_slot] : tm.a;
-    const double fr = tm.f_slot >= 0 ? params[tm.f_slot] : tm.f;
-    double ph = tm.phi_slot >= 0 ? params[tm.phi_slot] : tm.phi;
-    const int kind = tm.kind;
-    if (kind >= MSS_TERM_PWC) {
-      const double x = (t - tm.seg_t0) / tm.seg_len;
-      const double fl = floor(x);
-      int s = fl < 0.0 ? 0 : (fl > (double)(tm.n_seg - 1) ? tm.n_seg - 1 : (int)fl);
-      if (tm.seg_a_slot >= 0) amp = params[tm.seg_a_slot + s];
-      if (tm.seg_phi_slot >= 0) ph = params[tm.seg_phi_slot + s];
-    }
-    double v;
-    if (kind == MSS_TERM_CONST || kind == MSS_TERM_PWC) {
-      v = amp;
-    } else {
-      const double ft = fr * t;
-      const double x = kTwoPi * ft;
-      const double arg = x + ph;
-      double sn, cs;
-      sincos_cw(arg, &sn, &cs);
-      v = amp * ((kind == MSS_TERM_COS || kind == MSS_TERM_PWC_COS) ? cs : sn);
-    }
-    switch (tm.comp) {
-      case 0: f[0] = f[0] + v; break;
-      case 1: f[1] = f[1] + v; break;
-      case 2: f[2] = f[2] + v; break;
-      case 3: f[3] = f[3] + v; break;
-      case 4: f[4] = f[4] + v; break;
-      case 5: f[5] = f[5] + v; break;
-      case 6: f[6] = f[6] + v; break;
-      default: f[7] = f[7] + v; break;
-    }
-  }
-}
-
 // Node field in the rotating frame: (x + i y) and (v1 + i v2) times
 // e^{-i wr tau}, (u1 + i u2) times e^{-2i wr tau} (Delta m = 1 and 2 under
 // rotations about z), z - wr; (c, s) = (cos, sin)(wr tau).
@@ -967,18 +996,17 @@ __device__ __forceinline__ void frame_full(double w[kFullComps], double c, doubl
 
 template <class Terms>
 __device__ __forceinline__ void cf4_angles_full(const Terms& fp, const double* __restrict__ params,
-                                                double tk, int l, double dt, double wr,
-                                                const NodeRotations& rot,
+                                                const double (&fc)[kFullComps], double tk, int l,
+                                                double dt, double wr, const NodeRotations& rot,
                                                 double th1[kFullComps], double th2[kFullComps]) {
 #pragma clang fp contract(off)
+  const double t[2] = {tk + node_offset(0, l, dt), tk + node_offset(1, l, dt)};
   double w[2][kFullComps];
+  field_at(fp, params, fc, t, w);
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const double tau_i = ((double)l + (i == 0 ? kNode1 : kNode2)) * dt;
-    double f[kFullComps];
-    field_eval_full(fp, params, tk + tau_i, f);
 #pragma unroll
-    for (int j = 0; j < kFullComps; ++j) w[i][j] = kTwoPi * f[j];
+    for (int j = 0; j < kFullComps; ++j) w[i][j] = kTwoPi * w[i][j];
     if (wr != 0.0) frame_full(w[i], rot.c[i], rot.s[i], wr);
   }
 #pragma unroll
@@ -990,8 +1018,9 @@ __device__ __forceinline__ void cf4_angles_full(const Terms& fp, const double* _
 
 template <class Terms>
 __device__ __forceinline__ void euler_angles_full(const Terms& fp,
-                                                  const double* __restrict__ params, double tk,
-                                                  int l, double dt, double wr, int method,
+                                                  const double* __restrict__ params,
+                                                  const double (&fc)[kFullComps], double tk, int l,
+                                                  double dt, double wr, int method,
                                                   double th[kFullComps]) {
 #pragma clang fp contract(off)
   const int nn = method == 1 ? 1 : 2;
@@ -1001,10 +1030,11 @@ __device__ __forceinline__ void euler_angles_full(const Terms& fp,
     if (i >= nn) break;
     const double c = method == 1 ? 0.5 : (i == 0 ? 0.0 : 1.0);
     const double tau_i = ((double)l + c) * dt;
-    double f[kFullComps];
-    field_eval_full(fp, params, tk + tau_i, f);
+    const double t[1] = {tk + tau_i};
+    double f[1][kFullComps];
+    field_at(fp, params, fc, t, f);
 #pragma unroll
-    for (int j = 0; j < kFullComps; ++j) w[i][j] = kTwoPi * f[j];
+    for (int j = 0; j < kFullComps; ++j) w[i][j] = kTwoPi * f[0][j];
     if (wr != 0.0) {
       double s, cs;
       sincos_cw(wr * tau_i, &s, &cs);
@@ -1180,7 +1210,10 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
   R.clear();
   double tk = 0.0, wr = 0.0;
   if (active) {
-    interval_setup(terms, params, t_start, Dt, k, frame, &tk, &wr);
+    constexpr int C = FULL ? kFullComps : 4;
+    double fc[C];
+    field_constant(terms, params, fc);
+    interval_setup(terms, params, fc, t_start, Dt, k, frame, &tk, &wr);
     const int l0 = (int)(((int64_t)s * L) >> sl);
     const int l1 = (int)(((int64_t)(s + 1) * L) >> sl);
     const int slot = SHARE ? wave_slot() : 0;
@@ -1191,7 +1224,7 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
         for (int l = l0; l < l1; ++l) {
           if constexpr (SHARE) rotate_priority(l, slot);
           double th1[kFullComps], th2[kFullComps];
-          cf4_angles_full(terms, params, tk, l, dt, wr, rot, th1, th2);
+          cf4_angles_full(terms, params, fc, tk, l, dt, wr, rot, th1, th2);
           if (wr != 0.0) rot.advance();
           Mat<3> E;
           exp_full(th1, tau, E);
@@ -1203,7 +1236,7 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
         for (int l = l0; l < l1; ++l) {
           if constexpr (SHARE) rotate_priority(l, slot);
           double th[kFullComps];
-          euler_angles_full(terms, params, tk, l, dt, wr, method, th);
+          euler_angles_full(terms, params, fc, tk, l, dt, wr, method, th);
           Mat<3> E;
           exp_full(th, tau, E);
           R.multiply(E, l == l0);
@@ -1215,7 +1248,7 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
       for (int l = l0; l < l1; ++l) {
         if constexpr (SHARE) rotate_priority(l, slot);
         double th1[4], th2[4];
-        cf4_angles(terms, params, tk, l, dt, wr, rot, th1, th2);
+        cf4_angles(terms, params, fc, tk, l, dt, wr, rot, th1, th2);
         if (wr != 0.0) rot.advance();
         Mat<N> E;
         Exponentiator<N>::apply(th1, tau, E);
@@ -1227,7 +1260,7 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
       for (int l = l0; l < l1; ++l) {
         if constexpr (SHARE) rotate_priority(l, slot);
         double th[4];
-        euler_angles(terms, params, tk, l, dt, wr, method, th);
+        euler_angles(terms, params, fc, tk, l, dt, wr, method, th);
         Mat<N> E;
         Exponentiator<N>::apply(th, tau, E);
         R.multiply(E, l == l0);
@@ -1272,7 +1305,7 @@ struct IntervalGrid {
 // Lane body of the single-simulation integrator: one lane per (interval k,
 // slice s), the S = 2^sl slices of an interval in consecutive lanes of one
 // wave; the whole wave must call it.  `terms` is any field source
-// field_eval accepts.
+// field_at accepts.
 template <int N, class Terms>
 __device__ __forceinline__ void integrate_lanes(const Terms& terms, const IntervalGrid& g) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -48,6 +48,13 @@ mss_status api_resolve_launch(const mss_problem* p, const mss_launch* in, int* s
 // lane segments of a grid launch with S0 slices (IntervalGrid), given the
 // number of waves that run at once (slots; 0: unknown, one segment)
 void api_plan_lane_segments(IntervalGrid& g, int S0, bool given, int64_t slots);
+// A term list in the order the interpreter walks it, into out[0 .. n): first
+// the terms of components that depend on time (list order), then those of
+// components all of whose terms are constant and always on, whose field is
+// formed once per interval.  Components are summed apart, each in list
+// order, so the field is the list's bit for bit.  Returns the count of the
+// first kind.
+int program_order(const mss_term* terms, int n, mss_term* out);
 // waves of a planned grid launch
 int64_t api_grid_waves(const IntervalGrid& g);
 // waves of integrate_kernel<N> in blocks of `block` threads that run at once

@@ -18,14 +18,27 @@ __device__ void mss_user_field(double t, const double* params, double* field);
 
 struct MssUserField {};
 
-// Found by argument-dependent lookup from the interval operator's templates.
-__device__ __forceinline__ void field_eval(const MssUserField&, const double* __restrict__ params,
-                                           double t, double f[4]) {
-  f[0] = 0.0;
-  f[1] = 0.0;
-  f[2] = 0.0;
-  f[3] = 0.0;
-  mss_user_field(t, params, f);
+// Found by argument-dependent lookup from the interval operator's templates:
+// nothing of a user's field is known to be constant, and every time is a
+// call of its own.
+template <int C>
+__device__ __forceinline__ void field_constant(const MssUserField&, const double* __restrict__,
+                                               double (&fc)[C]) {
+#pragma unroll
+  for (int j = 0; j < C; ++j) fc[j] = 0.0;
+}
+template <int C, int M>
+__device__ __forceinline__ void field_at(const MssUserField&, const double* __restrict__ params,
+                                         const double (&)[C], const double (&t)[M],
+                                         double (&f)[M][C], int = -1) {
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    f[i][0] = 0.0;
+    f[i][1] = 0.0;
+    f[i][2] = 0.0;
+    f[i][3] = 0.0;
+    mss_user_field(t[i], params, f[i]);
+  }
 }
 
 extern "C" __global__ void __launch_bounds__(256) mss_user_integrate_2(const mss::IntervalGrid g) {

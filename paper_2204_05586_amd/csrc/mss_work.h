@@ -54,7 +54,7 @@ struct WorkSet {
 
  private:
   const mss_term* last_terms_ = nullptr;
-  int last_n_terms_ = -1, last_term_off_ = -1;
+  int last_n_terms_ = -1, last_term_off_ = -1, last_n_varying_ = 0;
 };
 
 // Device view of an uploaded work set.

@@ -67,7 +67,7 @@ __global__ void work_reset_kernel(unsigned long long* counter) {
 struct TableSource {
   __device__ __forceinline__ TableTerms operator()(const IntegrateWorkArgs& A,
                                                    const SimDesc& s) const {
-    return TableTerms{A.terms + s.term_off, s.n_terms};
+    return TableTerms{A.terms + s.term_off, s.n_terms, s.n_varying};
   }
 };
 
@@ -187,12 +187,15 @@ void WorkSet::add(const mss_problem& p, int slices_log2, int64_t k_first, int64_
   if (last_terms_ && last_n_terms_ == p.n_terms &&
       (p.n_terms == 0 || memcmp(last_terms_, p.terms, sizeof(mss_term) * p.n_terms) == 0)) {
     d.term_off = last_term_off_;
+    d.n_varying = last_n_varying_;
   } else {
     d.term_off = (int32_t)terms.size();
-    for (int t = 0; t < p.n_terms; ++t) terms.push_back(p.terms[t]);
+    terms.resize(terms.size() + p.n_terms);
+    d.n_varying = program_order(p.terms, p.n_terms, terms.data() + d.term_off);
     last_terms_ = p.terms;
     last_n_terms_ = p.n_terms;
     last_term_off_ = d.term_off;
+    last_n_varying_ = d.n_varying;
   }
   sims.push_back(d);
 }

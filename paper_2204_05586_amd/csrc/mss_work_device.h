@@ -23,6 +23,7 @@ struct SimDesc {
   int32_t spin_twice, n_terms, term_off, n_fine;
   int32_t tau, frame, slices_log2, top;  // top: scan levels above 0; -1: no scan
   int32_t method, full;  // full: spin-1 in the full su(3) basis
+  int32_t n_varying, pad;  // terms of components that depend on time (program_order)
 };
 
 // Chained runs: the states are formed inside the integrator's launch.  Each
