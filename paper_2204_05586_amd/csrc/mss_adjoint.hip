@@ -443,6 +443,8 @@ struct AdjDesc {
   int32_t tau, frame, n_gterms;
   uint32_t same_phase;           // bit n: term n's phase is that of term n - 1 (same_phase below)
   int32_t gterm[kMaxGradTerms];  // indices (within the simulation's terms) of terms with slots
+  uint32_t gterms;               // the same as bits
+  uint32_t pad;
 };
 
 struct AdjArgs {
@@ -457,7 +459,7 @@ struct GradAcc {
   double a, f, ph;  // d loss / d (amplitude, frequency, phase) of the current segment
 };
 
-__device__ __forceinline__ void flush(const mss_term& tm, GradAcc& g, double* grad) {
+__device__ __forceinline__ void flush(Constant<mss_term>& tm, GradAcc& g, double* grad) {
   int a_slot = tm.a_slot, phi_slot = tm.phi_slot;
   if (tm.kind >= MSS_TERM_PWC && g.seg >= 0) {
     if (tm.seg_a_slot >= 0) a_slot = tm.seg_a_slot + g.seg;
@@ -482,75 +484,100 @@ struct KeptTerms {
   int seg[2][kMaxGradTerms][kAdjointBlock];
 };
 
-// The field at node i's time t (the interpreter's arithmetic of field_at),
-// keeping the parameterised terms' derivatives.  A term marked in same_phase
-// has the window, segments, frequency and phase of the term before it and
-// takes that one's segment, sine and cosine.
-__device__ __forceinline__ void field_keep(const AdjDesc& s, const mss_term* __restrict__ terms,
-                                           double t, int i, KeptTerms& kept, double f[4]) {
+// The field at both nodes' times in one walk over the terms (the
+// interpreter's arithmetic of field_at), keeping the parameterised terms'
+// derivatives.  A term marked in same_phase has the window, segments,
+// frequency and phase of the term before it and takes that one's segments,
+// sines and cosines.
+__device__ __forceinline__ void field_keep(const AdjDesc& s, const mss_term* terms,
+                                           const double (&t)[2], KeptTerms& kept,
+                                           double (&f)[2][4]) {
 #pragma clang fp contract(off)
   const double* __restrict__ params = s.params;
   const int me = threadIdx.x;
-  double fx = 0.0, fy = 0.0, fz = 0.0, fq = 0.0;
-  double sn = 0.0, cs = 1.0;
-  int seg = -1, g = 0;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[i][j] = 0.0;
+  double sn[2] = {0.0, 0.0}, cs[2] = {1.0, 1.0};
+  int seg[2] = {-1, -1}, g = 0;
   for (int n = 0; n < s.n_terms; ++n) {
-    const mss_term& tm = terms[s.term_off + n];
+    Constant<mss_term>& tm = as_constant(terms)[s.term_off + n];
     // g stays uniform across the wave: it moves on whether or not the term is on
-    const bool keep = g < s.n_gterms && s.gterm[g] == n;
+    const bool keep = (s.gterms >> n) & 1;
     const int at = g;
     g += keep ? 1 : 0;
-    if (!(tm.t_on < t && t < tm.t_off)) {
-      if (keep) kept.seg[i][at][me] = -2;
+    const double t_on = tm.t_on, t_off = tm.t_off;
+    const bool on[2] = {t_on < t[0] && t[0] < t_off, t_on < t[1] && t[1] < t_off};
+    if (!(on[0] || on[1])) {
+      if (keep) kept.seg[0][at][me] = kept.seg[1][at][me] = -2;
       continue;
     }
-    const int kind = tm.kind;
+    const int kind = tm.kind, comp = tm.comp;
     const bool again = (s.same_phase >> n) & 1;
-    double amp = tm.a_slot >= 0 ? params[tm.a_slot] : tm.a;
+    const double a = tm.a_slot >= 0 ? as_constant(params)[tm.a_slot] : tm.a;
+    double amp[2] = {a, a};
     if (kind >= MSS_TERM_PWC) {
       if (!again) {
-        const double x = (t - tm.seg_t0) / tm.seg_len;
-        const double fl = floor(x);
-        seg = fl < 0.0 ? 0 : (fl > (double)(tm.n_seg - 1) ? tm.n_seg - 1 : (int)fl);
+        const double t0 = tm.seg_t0, len = tm.seg_len;
+        const int last = tm.n_seg - 1;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const double x = (t[i] - t0) / len;
+          const double fl = floor(x);
+          seg[i] = fl < 0.0 ? 0 : (fl > (double)last ? last : (int)fl);
+        }
       }
-      if (tm.seg_a_slot >= 0) amp = params[tm.seg_a_slot + seg];
+      if (tm.seg_a_slot >= 0) {
+        amp[0] = params[tm.seg_a_slot + seg[0]];
+        amp[1] = params[tm.seg_a_slot + seg[1]];
+      }
     } else {
-      seg = -1;
+      seg[0] = seg[1] = -1;
     }
-    double val = 1.0, dphase = 0.0;
+    double val[2] = {1.0, 1.0}, dphase[2] = {0.0, 0.0};
     if (kind != MSS_TERM_CONST && kind != MSS_TERM_PWC) {
       if (!again) {
-        const double fr = tm.f_slot >= 0 ? params[tm.f_slot] : tm.f;
-        double ph = tm.phi_slot >= 0 ? params[tm.phi_slot] : tm.phi;
-        if (kind >= MSS_TERM_PWC && tm.seg_phi_slot >= 0) ph = params[tm.seg_phi_slot + seg];
-        const double ft = fr * t;
-        const double x = kTwoPi * ft;
-        const double arg = x + ph;
-        sincos_cw(arg, &sn, &cs);
+        const double fr = tm.f_slot >= 0 ? as_constant(params)[tm.f_slot] : tm.f;
+        const double phi = tm.phi_slot >= 0 ? as_constant(params)[tm.phi_slot] : tm.phi;
+        double arg[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          double ph = phi;
+          if (kind >= MSS_TERM_PWC && tm.seg_phi_slot >= 0) ph = params[tm.seg_phi_slot + seg[i]];
+          const double ft = fr * t[i];
+          const double x = kTwoPi * ft;
+          arg[i] = x + ph;
+        }
+        sincos_cw(arg, sn, cs);
       }
       const bool is_cos = kind == MSS_TERM_COS || kind == MSS_TERM_PWC_COS;
-      val = is_cos ? cs : sn;
-      dphase = is_cos ? -amp * sn : amp * cs;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        val[i] = is_cos ? cs[i] : sn[i];
+        dphase[i] = is_cos ? -amp[i] * sn[i] : amp[i] * cs[i];
+      }
     }
-    const double v = amp * val;
-    switch (tm.comp) {
-      case 0: fx = fx + v; break;
-      case 1: fy = fy + v; break;
-      case 2: fz = fz + v; break;
-      default: fq = fq + v; break;
-    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (comp == j) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) f[i][j] = on[i] ? f[i][j] + amp[i] * val[i] : f[i][j];
+      }
     if (keep) {
-      kept.val[i][at][me] = val;
-      kept.dphase[i][at][me] = dphase;
-      kept.seg[i][at][me] = seg;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        kept.val[i][at][me] = val[i];
+        kept.dphase[i][at][me] = dphase[i];
+        kept.seg[i][at][me] = on[i] ? seg[i] : -2;
+      }
     }
   }
-  f[0] = fx; f[1] = fy; f[2] = fz; f[3] = fq;
 }
 
 // Contribution of node i (time t, d loss / d f_x, f_y = Gx, Gy) to the
 // gradient accumulators of the simulation's parameterised terms.
-__device__ __forceinline__ void node_grad(const AdjDesc& s, const mss_term* __restrict__ terms,
+__device__ __forceinline__ void node_grad(const AdjDesc& s, const mss_term* terms,
                                           double t, int i, const KeptTerms& kept, double Gx,
                                           double Gy, GradAcc* acc) {
 #pragma clang fp contract(off)
@@ -560,7 +587,7 @@ __device__ __forceinline__ void node_grad(const AdjDesc& s, const mss_term* __re
     if (g >= s.n_gterms) break;
     const int seg = kept.seg[i][g][me];
     if (seg == -2) continue;
-    const mss_term& tm = terms[s.term_off + s.gterm[g]];
+    Constant<mss_term>& tm = as_constant(terms)[s.term_off + s.gterm[g]];
     const double G = tm.comp == MSS_X ? Gx : Gy;
     if (tm.kind >= MSS_TERM_PWC && seg != acc[g].seg) {
       if (acc[g].seg >= 0) flush(tm, acc[g], s.grad);
@@ -607,13 +634,11 @@ __device__ __forceinline__ void adjoint_interval(const AdjArgs& A, const AdjDesc
   rot.s[0] = rot.s[1] = 0.0;
   if (wr != 0.0) rot.start(wr, s.n_fine - 1, s.dt);
   for (int l = s.n_fine - 1; l >= 0; --l) {
-    double w[2][4], th[2][4];
+    const double t[2] = {tk + node_offset(0, l, s.dt), tk + node_offset(1, l, s.dt)};
+    double f[2][4], w[2][4], th[2][4];
+    field_keep(s, A.terms, t, kept, f);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      double f[4];
-      field_keep(s, A.terms, tk + node_offset(i, l, s.dt), i, kept, f);
-      node_rates(f, wr, rot.c[i], rot.s[i], w[i]);
-    }
+    for (int i = 0; i < 2; ++i) node_rates(f[i], wr, rot.c[i], rot.s[i], w[i]);
     cf4_combine(w, s.dt, th[0], th[1]);
     double gx[2] = {0.0, 0.0}, gy[2] = {0.0, 0.0};
 #pragma unroll 1
@@ -648,21 +673,23 @@ __device__ __forceinline__ void adjoint_interval(const AdjArgs& A, const AdjDesc
   }
 #pragma unroll
   for (int g = 0; g < kMaxGradTerms; ++g)
-    if (g < s.n_gterms) flush(A.terms[s.term_off + s.gterm[g]], acc[g], s.grad);
+    if (g < s.n_gterms) flush(as_constant(A.terms)[s.term_off + s.gterm[g]], acc[g], s.grad);
 }
 
 __global__ void __launch_bounds__(kAdjointBlock, 2) adjoint_kernel(const AdjArgs A) {
   __shared__ KeptTerms kept;  // every lane its own entries
   const int lane = threadIdx.x & 63;
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  // scalar, so that the descriptor and the terms are scalar loads
+  const int64_t wave = (int64_t)blockIdx.x * (blockDim.x >> 6) +
+                       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wave >= A.n_waves) return;
   int lo = 0, hi = A.n_sims - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (A.sims[mid].wave_off <= wave) lo = mid;
+    if (as_constant(A.sims)[mid].wave_off <= wave) lo = mid;
     else hi = mid - 1;
   }
-  const AdjDesc& s = A.sims[lo];
+  const AdjDesc s = load_constant(A.sims + lo);
   const int64_t k = (wave - s.wave_off) * 64 + lane;
   if (k >= s.K) return;
   if (s.spin_twice == 2) adjoint_interval<3>(A, s, k, kept);
@@ -988,8 +1015,10 @@ mss_status mss_adjoint_plan_create(int32_t n, const mss_problem* problems, const
       P->terms.push_back(tm);
       if (t > 0 && same_phase(q.terms[t - 1], tm)) a.same_phase |= 1u << t;
       if (tm.a_slot >= 0 || tm.f_slot >= 0 || tm.phi_slot >= 0 || tm.seg_a_slot >= 0 ||
-          tm.seg_phi_slot >= 0)
+          tm.seg_phi_slot >= 0) {
         a.gterm[a.n_gterms++] = t;
+        a.gterms |= 1u << t;
+      }
     }
     P->adj.push_back(a);
   }

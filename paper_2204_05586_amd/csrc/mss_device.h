@@ -44,6 +44,30 @@ struct has_full_basis<T, decltype((void)T::kFullBasis)> {
   static constexpr bool value = T::kFullBasis;
 };
 
+// Memory that no kernel writes while this one runs (descriptors, term tables,
+// parameters): read through the constant address space, a wave-uniform
+// address is a scalar load whatever the kernel stores in between.  Through
+// an ordinary pointer the compiler must assume that a store or atomic has
+// changed it, and every read inside a work loop becomes a vector load.
+template <class T>
+using Constant = const T __attribute__((address_space(4)));
+template <class T>
+__device__ __forceinline__ Constant<T>* as_constant(const T* p) {
+  return (Constant<T>*)(uint64_t)p;
+}
+// A whole structure of 8-byte words.
+template <class T>
+__device__ __forceinline__ T load_constant(const T* p) {
+  static_assert(sizeof(T) % 8 == 0, "8-byte words");
+  Constant<uint64_t>* src = (Constant<uint64_t>*)(uint64_t)p;
+  uint64_t w[sizeof(T) / 8];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 8; ++i) w[i] = src[i];
+  T v;
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
+}
+
 // Term sources for the interpreter: the kernel-argument program of a single
 // simulation, or a slice of a term table in device memory (batches).
 struct ArgTerms {
@@ -55,11 +79,13 @@ struct ArgTerms {
 };
 struct TableTerms {
   static constexpr bool kFullBasis = true;
-  const mss_term* __restrict__ t;
+  const mss_term* t;
   int n, n_varying;
   __device__ __forceinline__ int size() const { return n; }
   __device__ __forceinline__ int varying() const { return n_varying; }
-  __device__ __forceinline__ const mss_term& operator[](int i) const { return t[i]; }
+  __device__ __forceinline__ Constant<mss_term>& operator[](int i) const {
+    return as_constant(t)[i];
+  }
 };
 
 template <int N>
@@ -727,8 +753,8 @@ __device__ __forceinline__ void field_constant(const Terms& fp, const double* __
   for (int j = 0; j < C; ++j) fc[j] = 0.0;
   const int nt = fp.size();
   for (int n = fp.varying(); n < nt; ++n) {
-    const mss_term& tm = fp[n];
-    const double v = tm.a_slot >= 0 ? params[tm.a_slot] : tm.a;
+    const auto& tm = fp[n];
+    const double v = tm.a_slot >= 0 ? as_constant(params)[tm.a_slot] : tm.a;
     const int comp = tm.comp;
 #pragma unroll
     for (int j = 0; j < C; ++j)
@@ -755,7 +781,7 @@ __device__ __forceinline__ void field_at(const Terms& fp, const double* __restri
     for (int j = 0; j < C; ++j) f[i][j] = fc[j];
   const int nt = fp.varying();
   for (int n = 0; n < nt; ++n) {
-    const mss_term& tm = fp[n];
+    const auto& tm = fp[n];
     const int comp = tm.comp, kind = tm.kind;
     if (only >= 0 && comp != only) continue;
     const double t_on = tm.t_on, t_off = tm.t_off;
@@ -766,7 +792,7 @@ __device__ __forceinline__ void field_at(const Terms& fp, const double* __restri
       any = any || on[i];
     }
     if (!any) continue;
-    const double a = tm.a_slot >= 0 ? params[tm.a_slot] : tm.a;
+    const double a = tm.a_slot >= 0 ? as_constant(params)[tm.a_slot] : tm.a;
     double amp[M], v[M];
 #pragma unroll
     for (int i = 0; i < M; ++i) amp[i] = a;
@@ -786,8 +812,8 @@ __device__ __forceinline__ void field_at(const Terms& fp, const double* __restri
 #pragma unroll
       for (int i = 0; i < M; ++i) v[i] = amp[i];
     } else {
-      const double fr = tm.f_slot >= 0 ? params[tm.f_slot] : tm.f;
-      const double phi = tm.phi_slot >= 0 ? params[tm.phi_slot] : tm.phi;
+      const double fr = tm.f_slot >= 0 ? as_constant(params)[tm.f_slot] : tm.f;
+      const double phi = tm.phi_slot >= 0 ? as_constant(params)[tm.phi_slot] : tm.phi;
       double arg[M], sn[M], cs[M];
 #pragma unroll
       for (int i = 0; i < M; ++i) {

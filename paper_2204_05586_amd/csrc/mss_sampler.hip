@@ -101,7 +101,7 @@ std::string hex_literal(double v) {
 }
 
 std::string slot_or_literal(int32_t slot, double v) {
-  return slot >= 0 ? "p[" + std::to_string(slot) + "]" : hex_literal(v);
+  return slot >= 0 ? "pc[" + std::to_string(slot) + "]" : hex_literal(v);
 }
 
 // HIP source of mss_user_field for a term list: the field-program
@@ -115,6 +115,7 @@ std::string specialised_source(const mss_term* terms, int n) {
   s += "__device__ void mss_user_field(double t, const double* p, double* f) {\n";
   s += "#pragma clang fp contract(off)\n";
   s += "  double fc[4] = {0.0, 0.0, 0.0, 0.0};\n";
+  s += "  const auto* pc = mss::as_constant(p);\n";  // slots are wave-uniform
   for (int i = 0; i < n; ++i) {
     const mss_term& tm = terms[i];
     if (tm.t_on == INFINITY || tm.t_off == -INFINITY || !(tm.t_on < tm.t_off)) continue;

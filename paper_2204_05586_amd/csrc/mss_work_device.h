@@ -443,7 +443,7 @@ __device__ __forceinline__ void chained_integrate_loop(const IntegrateWorkArgs& 
     const int64_t cnt = A.group_count[lo];
     const int64_t round = wave_broadcast(A.group_round0[lo] + off / cnt);
     const int sim = __builtin_amdgcn_readfirstlane(A.order[off % cnt]);
-    const SimDesc& s = A.sims[sim];
+    const SimDesc s = load_constant(A.sims + sim);
     if (s.spin_twice == 2) chained_unit<3>(A, s, A.slots + sim, round, lane, lds, source);
     else chained_unit<2>(A, s, A.slots + sim, round, lane, lds, source);
     if (!ahead && lane == 0) next = (int64_t)atomicAdd(A.counter, 1ull);
@@ -469,7 +469,7 @@ __device__ __forceinline__ void work_integrate_loop(const IntegrateWorkArgs& A,
     int64_t next = 0;
     if (ahead && lane == 0) next = (int64_t)atomicAdd(A.counter, 1ull);
     const int lo = wave_search([&](int i) { return A.sims[i].item_off; }, A.n_sims, item, lane);
-    const SimDesc& s = A.sims[lo];
+    const SimDesc s = load_constant(A.sims + lo);
     const int64_t local = item - s.item_off;
     if (s.spin_twice == 2) work_item<3>(A, s, local, lane, source);
     else work_item<2>(A, s, local, lane, source);
