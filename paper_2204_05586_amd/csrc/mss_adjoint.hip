@@ -441,7 +441,7 @@ struct AdjDesc {
   const double* lam_before;    // costates: entry j = lambda_{K-j}, j < K
   int32_t spin_twice, n_terms, term_off, n_fine;
   int32_t tau, frame, n_gterms;
-  uint32_t same_phase;           // bit n: term n's phase is that of term n - 1 (same_phase below)
+  uint32_t same_phase;           // bit n: term n's phase is that of term n - 1 (same_phase)
   int32_t gterm[kMaxGradTerms];  // indices (within the simulation's terms) of terms with slots
   uint32_t gterms;               // the same as bits
   uint32_t pad;
@@ -803,26 +803,6 @@ void release(mss_adjoint_plan* P) {
   if (P->last_run) (void)hipEventDestroy(P->last_run);
   if (P->desc) (void)hipFree(P->desc);
   delete P;
-}
-
-// Whether b, the term after a, takes the same phase 2 pi f t + phi at every
-// time at which either is on (field_keep then evaluates it once): a
-// circular drive's cosine and sine.
-bool same_phase(const mss_term& a, const mss_term& b) {
-  const bool pwc = a.kind == MSS_TERM_PWC_COS || a.kind == MSS_TERM_PWC_SIN;
-  if (pwc != (b.kind == MSS_TERM_PWC_COS || b.kind == MSS_TERM_PWC_SIN)) return false;
-  if (!pwc && ((a.kind != MSS_TERM_COS && a.kind != MSS_TERM_SIN) ||
-               (b.kind != MSS_TERM_COS && b.kind != MSS_TERM_SIN)))
-    return false;
-  const auto same = [](int32_t sa, double va, int32_t sb, double vb) {
-    return sa >= 0 ? sa == sb : (sb < 0 && va == vb);
-  };
-  if (a.t_on != b.t_on || a.t_off != b.t_off || !same(a.f_slot, a.f, b.f_slot, b.f)) return false;
-  if (!pwc) return same(a.phi_slot, a.phi, b.phi_slot, b.phi);
-  if (a.n_seg != b.n_seg || a.seg_t0 != b.seg_t0 || a.seg_len != b.seg_len) return false;
-  return a.seg_phi_slot >= 0
-             ? a.seg_phi_slot == b.seg_phi_slot
-             : (b.seg_phi_slot < 0 && same(a.phi_slot, a.phi, b.phi_slot, b.phi));
 }
 
 void pack_all(mss_adjoint_plan* P) {

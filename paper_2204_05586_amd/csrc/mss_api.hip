@@ -278,6 +278,23 @@ void api_plan_lane_segments(IntervalGrid& g, int S0, bool given, int64_t slots) 
   g.seg_w0[1] = full;
 }
 
+bool same_phase(const mss_term& a, const mss_term& b) {
+  const bool pwc = a.kind == MSS_TERM_PWC_COS || a.kind == MSS_TERM_PWC_SIN;
+  if (pwc != (b.kind == MSS_TERM_PWC_COS || b.kind == MSS_TERM_PWC_SIN)) return false;
+  if (!pwc && ((a.kind != MSS_TERM_COS && a.kind != MSS_TERM_SIN) ||
+               (b.kind != MSS_TERM_COS && b.kind != MSS_TERM_SIN)))
+    return false;
+  const auto same = [](int32_t sa, double va, int32_t sb, double vb) {
+    return sa >= 0 ? sa == sb : (sb < 0 && va == vb);
+  };
+  if (a.t_on != b.t_on || a.t_off != b.t_off || !same(a.f_slot, a.f, b.f_slot, b.f)) return false;
+  if (!pwc) return same(a.phi_slot, a.phi, b.phi_slot, b.phi);
+  if (a.n_seg != b.n_seg || a.seg_t0 != b.seg_t0 || a.seg_len != b.seg_len) return false;
+  return a.seg_phi_slot >= 0
+             ? a.seg_phi_slot == b.seg_phi_slot
+             : (b.seg_phi_slot < 0 && same(a.phi_slot, a.phi, b.phi_slot, b.phi));
+}
+
 int program_order(const mss_term* terms, int n, mss_term* out) {
   unsigned varying = 0;  // components
   for (int i = 0; i < n; ++i)

@@ -153,18 +153,14 @@ template <int N> struct Running;
 template <> struct Running<3> {
   Mat<3> u;
   __device__ __forceinline__ void clear() { set_identity<3>(u); }
-  // the product so far times E on the left; the first is taken as it is
-  __device__ __forceinline__ void multiply(const Mat<3>& E, bool first) {
-    if (first) u = E;
-    else premultiply<3>(E, u);
-  }
+  __device__ __forceinline__ void multiply(const Mat<3>& E) { premultiply<3>(E, u); }
   __device__ __forceinline__ void whole(Mat<3>& U) const { U = u; }
 };
 template <> struct Running<2> {
   double r[2], i[2];
   __device__ __forceinline__ void clear() { r[0] = r[1] = i[0] = i[1] = 0.0; }
   // I + x <- (I + A) (I + x): x <- A x + (A + x), the first column
-  __device__ __forceinline__ void multiply(const Mat<2>& A, bool /*first*/) {
+  __device__ __forceinline__ void multiply(const Mat<2>& A) {
     double nr[2], ni[2];
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
@@ -266,10 +262,15 @@ __device__ __forceinline__ void store_mat(double* __restrict__ p, const Mat<N>& 
 // ---------------------------------------------------------------------------
 // sincos_cw: Cody-Waite reduction x = k pi/2 + r with pi/2 split into three
 // doubles (P1, P2 with 32 significant bits so k P1 and k P2 are exact for
-// |k| < 2^20; P3 the rest), then the Taylor series of sin r to r^17 and of
-// cos r to r^16 on |r| <= pi/4 (truncation < 1e-17), rotated by the
-// quadrant k mod 4.  Beyond |x| = 1.5 * 2^20 the reduction is no longer
-// exact and ocml's sincos is used.
+// |k| < 2^20; P3 the rest), then minimax polynomials of sin r and cos r on
+// |r| <= pi/4, rotated by the quadrant k mod 4.  The polynomials are from a
+// Remez exchange in 60 digits: sin r = r + r y S(y) and cos r = 1 - y / 2 +
+// y^2 C(y), y = r^2, S of degree 5 (relative error 2^-58) and C of degree 5
+// (2^-64).  4e6 arguments in each of |x| < 3, 1e3 and 4e5 are off by at most
+// 1.7e-16 and 3.5e-17 in the mean square, as with the Taylor series to r^17
+// and r^16 before them, in 3 steps less.  (One odd polynomial on
+// |r| <= pi/2 would do without the second: 2.1e-16 and 4.2e-17.)  Beyond
+// |x| = 1.5 * 2^20 the reduction is no longer exact and ocml's sincos is used.
 constexpr double kTwoOverPi = 0x1.45f306dc9c883p-1;
 constexpr double kPio2_1 = 0x1.921fb54400000p+0;
 constexpr double kPio2_2 = 0x1.0b4611a600000p-34;
@@ -278,55 +279,85 @@ constexpr double kPio2_3 = 0x1.3198a2e037073p-69;
 // |x| < 1.5 * 2^20 (NaN: no)
 __device__ __forceinline__ bool sincos_in_range(double x) { return fabs(x) < 0x1.8p+20; }
 
-// The reduction and series for an x in range.
-__device__ __forceinline__ void sincos_reduced(double x, double* s, double* c) {
-  const double k = rint(x * kTwoOverPi);
-  double r = fma(-k, kPio2_1, x);
-  r = fma(-k, kPio2_2, r);
-  r = fma(-k, kPio2_3, r);
-  const double r2 = r * r;
-  double ps = 0x1.952c77030ad4ap-49;          //  1/17!
-  ps = fma(ps, r2, -0x1.ae7f3e733b81fp-41);   // -1/15!
-  ps = fma(ps, r2, 0x1.6124613a86d09p-33);    //  1/13!
-  ps = fma(ps, r2, -0x1.ae64567f544e4p-26);   // -1/11!
-  ps = fma(ps, r2, 0x1.71de3a556c734p-19);    //  1/9!
-  ps = fma(ps, r2, -0x1.a01a01a01a01ap-13);   // -1/7!
-  ps = fma(ps, r2, 0x1.1111111111111p-7);     //  1/5!
-  ps = fma(ps, r2, -0x1.5555555555555p-3);    // -1/3!
-  const double sn = fma(r * r2, ps, r);
-  double pc = 0x1.ae7f3e733b81fp-45;          //  1/16!
-  pc = fma(pc, r2, -0x1.93974a8c07c9dp-37);   // -1/14!
-  pc = fma(pc, r2, 0x1.1eed8eff8d898p-29);    //  1/12!
-  pc = fma(pc, r2, -0x1.27e4fb7789f5cp-22);   // -1/10!
-  pc = fma(pc, r2, 0x1.a01a01a01a01ap-16);    //  1/8!
-  pc = fma(pc, r2, -0x1.6c16c16c16c17p-10);   // -1/6!
-  pc = fma(pc, r2, 0x1.5555555555555p-5);     //  1/4!
-  pc = fma(pc, r2, -0.5);                     // -1/2!
-  const double cn = fma(r2, pc, 1.0);
-  const int q = ((int)k) & 3;
-  const double s1 = (q & 1) ? cn : sn;
-  const double c1 = (q & 1) ? sn : cn;
-  *s = (q & 2) ? -s1 : s1;
-  *c = ((q + 1) & 2) ? -c1 : c1;
+// A constant as a scalar operand.  Left to itself the compiler forms each
+// step of a Horner chain in place of its constant (a two-operand multiply-
+// add), which takes a vector move per coefficient: 15 of the 48 instructions
+// of a sine and cosine.  A scalar constant is moved beside the vector work
+// and serves every chain that uses it.
+__device__ __forceinline__ double scalar_constant(double c) {
+  asm("" : "+s"(c));
+  return c;
 }
 
-__device__ __forceinline__ void sincos_cw(double x, double* s, double* c) {
-  if (sincos_in_range(x)) sincos_reduced(x, s, c);
-  else sincos(x, s, c);
+// The reduction and series for M arguments in range, the chains side by side.
+template <int M>
+__device__ __forceinline__ void sincos_reduced(const double (&x)[M], double (&s)[M],
+                                               double (&c)[M]) {
+  constexpr double kSin[6] = {0x1.5d932f4b3062ep-33, -0x1.ae5e66d4cdfebp-26,
+                              0x1.71de357874087p-19, -0x1.a01a019c126a4p-13,
+                              0x1.111111110f880p-7,  -0x1.5555555555549p-3};
+  constexpr double kCos[7] = {-0x1.8faecfa48eeadp-37, 0x1.1ee9ec48989bcp-29,
+                              -0x1.27e4f80a77ac2p-22, 0x1.a01a019cb270cp-16,
+                              -0x1.6c16c16c15184p-10, 0x1.555555555554cp-5, -0.5};
+  double k[M], r[M], r2[M], ps[M], pc[M];
+  const double over = scalar_constant(kTwoOverPi);
+  const double p1 = scalar_constant(kPio2_1), p2 = scalar_constant(kPio2_2),
+               p3 = scalar_constant(kPio2_3);
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    k[i] = rint(x[i] * over);
+    r[i] = fma(-k[i], p1, x[i]);
+    r[i] = fma(-k[i], p2, r[i]);
+    r[i] = fma(-k[i], p3, r[i]);
+    r2[i] = r[i] * r[i];
+    ps[i] = kSin[0];
+    pc[i] = kCos[0];
+  }
+#pragma unroll
+  for (int j = 1; j < 6; ++j) {
+    const double a = scalar_constant(kSin[j]), b = scalar_constant(kCos[j]);
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      ps[i] = fma(ps[i], r2[i], a);
+      pc[i] = fma(pc[i], r2[i], b);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    const double sn = fma(r[i] * r2[i], ps[i], r[i]);
+    const double cn = fma(r2[i], fma(pc[i], r2[i], kCos[6]), 1.0);
+    const int q = ((int)k[i]) & 3;
+    const double s1 = (q & 1) ? cn : sn;
+    const double c1 = (q & 1) ? sn : cn;
+    s[i] = (q & 2) ? -s1 : s1;
+    c[i] = ((q + 1) & 2) ? -c1 : c1;
+  }
 }
 
-// Of M arguments at once: with all in range there is one branch and the M
-// chains of dependent operations run side by side.
+// Of M arguments at once: one branch for all (ocml's sincos for all of them
+// when one is out of range).
 template <int M>
 __device__ __forceinline__ void sincos_cw(const double (&x)[M], double (&s)[M], double (&c)[M]) {
   bool all = true;
 #pragma unroll
   for (int i = 0; i < M; ++i) all = all && sincos_in_range(x[i]);
   if (all) {
-#pragma unroll
-    for (int i = 0; i < M; ++i) sincos_reduced(x[i], &s[i], &c[i]);
+    sincos_reduced(x, s, c);
   } else {
-    for (int i = 0; i < M; ++i) sincos_cw(x[i], &s[i], &c[i]);
+#pragma unroll
+    for (int i = 0; i < M; ++i) sincos(x[i], &s[i], &c[i]);
+  }
+}
+
+__device__ __forceinline__ void sincos_cw(double x, double* s, double* c) {
+  if (sincos_in_range(x)) {
+    const double xi[1] = {x};
+    double si[1], ci[1];
+    sincos_reduced(xi, si, ci);
+    *s = si[0];
+    *c = ci[0];
+  } else {
+    sincos(x, s, c);
   }
 }
 
@@ -762,6 +793,14 @@ __device__ __forceinline__ void field_constant(const Terms& fp, const double* __
   }
 }
 
+template <int M>
+__device__ __forceinline__ bool any_of(const bool (&on)[M]) {
+  bool any = false;
+#pragma unroll
+  for (int i = 0; i < M; ++i) any = any || on[i];
+  return any;
+}
+
 // field_at: the whole field at M times, the constant part given: one walk
 // over the varying terms for all of them (each term is read once, and the M
 // chains of dependent operations run side by side).  only >= 0: no other
@@ -785,13 +824,10 @@ __device__ __forceinline__ void field_at(const Terms& fp, const double* __restri
     const int comp = tm.comp, kind = tm.kind;
     if (only >= 0 && comp != only) continue;
     const double t_on = tm.t_on, t_off = tm.t_off;
-    bool on[M], any = false;
+    bool on[M];
 #pragma unroll
-    for (int i = 0; i < M; ++i) {
-      on[i] = t_on < t[i] && t[i] < t_off;
-      any = any || on[i];
-    }
-    if (!any) continue;
+    for (int i = 0; i < M; ++i) on[i] = t_on < t[i] && t[i] < t_off;
+    if (!any_of(on)) continue;
     const double a = tm.a_slot >= 0 ? as_constant(params)[tm.a_slot] : tm.a;
     double amp[M], v[M];
 #pragma unroll
@@ -1254,9 +1290,9 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
           if (wr != 0.0) rot.advance();
           Mat<3> E;
           exp_full(th1, tau, E);
-          R.multiply(E, l == l0);
+          R.multiply(E);
           exp_full(th2, tau, E);
-          R.multiply(E, false);
+          R.multiply(E);
         }
       } else {
         for (int l = l0; l < l1; ++l) {
@@ -1265,7 +1301,7 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
           euler_angles_full(terms, params, fc, tk, l, dt, wr, method, th);
           Mat<3> E;
           exp_full(th, tau, E);
-          R.multiply(E, l == l0);
+          R.multiply(E);
         }
       }
     } else if (method == 0) {
@@ -1278,9 +1314,9 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
         if (wr != 0.0) rot.advance();
         Mat<N> E;
         Exponentiator<N>::apply(th1, tau, E);
-        R.multiply(E, l == l0);
+        R.multiply(E);
         Exponentiator<N>::apply(th2, tau, E);
-        R.multiply(E, false);
+        R.multiply(E);
       }
     } else {
       for (int l = l0; l < l1; ++l) {
@@ -1289,7 +1325,7 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
         euler_angles(terms, params, fc, tk, l, dt, wr, method, th);
         Mat<N> E;
         Exponentiator<N>::apply(th, tau, E);
-        R.multiply(E, l == l0);
+        R.multiply(E);
       }
     }
   }

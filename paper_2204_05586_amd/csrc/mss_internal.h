@@ -48,6 +48,10 @@ mss_status api_resolve_launch(const mss_problem* p, const mss_launch* in, int* s
 // lane segments of a grid launch with S0 slices (IntervalGrid), given the
 // number of waves that run at once (slots; 0: unknown, one segment)
 void api_plan_lane_segments(IntervalGrid& g, int S0, bool given, int64_t slots);
+// Whether b, the term after a, takes the same phase 2 pi f t + phi at every
+// time at which either is on, and the same segments: a circular drive's
+// cosine and sine, evaluated once then.
+bool same_phase(const mss_term& a, const mss_term& b);
 // A term list in the order the interpreter walks it, into out[0 .. n): first
 // the terms of components that depend on time (list order), then those of
 // components all of whose terms are constant and always on, whose field is

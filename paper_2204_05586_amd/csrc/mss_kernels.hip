@@ -13,7 +13,7 @@ namespace mss {
 // [s L / S, (s + 1) L / S) and the partial products are combined in order
 // (later slices on the left) with wave shuffles.
 template <int N>
-__global__ void __launch_bounds__(256) integrate_kernel(const IntegrateArgs A) {
+__global__ void __launch_bounds__(256, 2) integrate_kernel(const IntegrateArgs A) {
   integrate_lanes<N>(ArgTerms{A.fp}, A.g);
 }
 

@@ -104,53 +104,74 @@ std::string slot_or_literal(int32_t slot, double v) {
   return slot >= 0 ? "pc[" + std::to_string(slot) + "]" : hex_literal(v);
 }
 
-// HIP source of mss_user_field for a term list: the field-program
-// interpreter's operations for these terms, in the same order and with the
-// same contraction (none), so that the compiled integrator reproduces the
+// HIP source of a term list's field at M times at once
+// (MSS_TERMS_FIELD, mss_user_kernels.h): the field-program interpreter's
+// operations for these terms, in the same order and with the same
+// contraction (none), so that the compiled integrator reproduces the
 // interpreter's operators bit for bit.  Window bounds that are infinite are
-// left out (every finite t passes them); a term whose window holds no
-// finite time is left out altogether.
+// left out (every finite t passes them), and so is a term whose window holds
+// no finite time.  A term whose phase is that of the term before it takes
+// that one's segments, sines and cosines.  (Both nodes of a fine step in one
+// evaluation, and a circular drive's sine and cosine as one: the forward
+// pass of 256 control instances 868 -> 763 us.)
 std::string specialised_source(const mss_term* terms, int n) {
   std::string s;
-  s += "__device__ void mss_user_field(double t, const double* p, double* f) {\n";
+  s += "#define MSS_TERMS_FIELD 1\n";
+  s += "template <int M>\n";
+  s += "__device__ __forceinline__ void mss_terms_field(const double (&t)[M], const double* p, "
+       "double (&f)[M][4]) {\n";
   s += "#pragma clang fp contract(off)\n";
-  s += "  double fc[4] = {0.0, 0.0, 0.0, 0.0};\n";
+  s += "  for (int i = 0; i < M; ++i) f[i][0] = f[i][1] = f[i][2] = f[i][3] = 0.0;\n";
   s += "  const auto* pc = mss::as_constant(p);\n";  // slots are wave-uniform
-  for (int i = 0; i < n; ++i) {
-    const mss_term& tm = terms[i];
+  s += "  double sn[M], cs[M];\n  int seg[M];\n  bool on[M];\n";
+  int before = -1;  // the list's last term with code
+  for (int k = 0; k < n; ++k) {
+    const mss_term& tm = terms[k];
     if (tm.t_on == INFINITY || tm.t_off == -INFINITY || !(tm.t_on < tm.t_off)) continue;
+    const bool again = before >= 0 && same_phase(terms[before], tm);
+    before = k;
+    const std::string comp = std::to_string(tm.comp);
     std::string cond;
-    if (tm.t_on != -INFINITY) cond = hex_literal(tm.t_on) + " < t";
-    if (tm.t_off != INFINITY) cond += (cond.empty() ? "" : " && ") + std::string("t < ") + hex_literal(tm.t_off);
-    s += "  // term " + std::to_string(i) + "\n";
-    s += cond.empty() ? "  {\n" : "  if (" + cond + ") {\n";
-    s += "    double amp = " + slot_or_literal(tm.a_slot, tm.a) + ";\n";
-    s += "    double ph = " + slot_or_literal(tm.phi_slot, tm.phi) + ";\n";
-    if (tm.kind >= MSS_TERM_PWC) {
-      s += "    const double x = (t - " + hex_literal(tm.seg_t0) + ") / " + hex_literal(tm.seg_len) +
-           ";\n";
-      s += "    const double fl = floor(x);\n";
-      s += "    const int s = fl < 0.0 ? 0 : (fl > (double)(" + std::to_string(tm.n_seg - 1) +
-           ") ? " + std::to_string(tm.n_seg - 1) + " : (int)fl);\n";
-      if (tm.seg_a_slot >= 0) s += "    amp = p[" + std::to_string(tm.seg_a_slot) + " + s];\n";
-      if (tm.seg_phi_slot >= 0) s += "    ph = p[" + std::to_string(tm.seg_phi_slot) + " + s];\n";
+    if (tm.t_on != -INFINITY) cond = hex_literal(tm.t_on) + " < t[i]";
+    if (tm.t_off != INFINITY)
+      cond += (cond.empty() ? "" : " && ") + std::string("t[i] < ") + hex_literal(tm.t_off);
+    s += "  // term " + std::to_string(k) + "\n";
+    if (!cond.empty() && !again) s += "  for (int i = 0; i < M; ++i) on[i] = " + cond + ";\n";
+    s += cond.empty() ? "  {\n" : "  if (mss::any_of(on)) {\n";
+    const bool pwc = tm.kind >= MSS_TERM_PWC;
+    if (pwc && !again) {
+      const std::string last = std::to_string(tm.n_seg - 1);
+      s += "    for (int i = 0; i < M; ++i) {\n";
+      s += "      const double x = (t[i] - " + hex_literal(tm.seg_t0) + ") / " +
+           hex_literal(tm.seg_len) + ";\n";
+      s += "      const double fl = floor(x);\n";
+      s += "      seg[i] = fl < 0.0 ? 0 : (fl > (double)(" + last + ") ? " + last +
+           " : (int)fl);\n    }\n";
     }
-    if (tm.kind == MSS_TERM_CONST || tm.kind == MSS_TERM_PWC) {
-      s += "    const double v = amp;\n";
-    } else {
-      const bool is_cos = tm.kind == MSS_TERM_COS || tm.kind == MSS_TERM_PWC_COS;
-      s += "    const double fr = " + slot_or_literal(tm.f_slot, tm.f) + ";\n";
-      s += "    const double ft = fr * t;\n";
-      s += "    const double xr = mss::kTwoPi * ft;\n";
-      s += "    const double arg = xr + ph;\n";
-      s += "    double sn, cs;\n";
-      s += "    mss::sincos_cw(arg, &sn, &cs);\n";
-      s += std::string("    const double v = amp * ") + (is_cos ? "cs" : "sn") + ";\n";
+    const bool constant = tm.kind == MSS_TERM_CONST || tm.kind == MSS_TERM_PWC;
+    if (!constant && !again) {
+      s += "    double arg[M];\n    for (int i = 0; i < M; ++i) {\n";
+      s += "      double ph = " + slot_or_literal(tm.phi_slot, tm.phi) + ";\n";
+      if (pwc && tm.seg_phi_slot >= 0)
+        s += "      ph = p[" + std::to_string(tm.seg_phi_slot) + " + seg[i]];\n";
+      s += "      const double fr = " + slot_or_literal(tm.f_slot, tm.f) + ";\n";
+      s += "      const double ft = fr * t[i];\n";
+      s += "      const double xr = mss::kTwoPi * ft;\n";
+      s += "      arg[i] = xr + ph;\n    }\n";
+      s += "    mss::sincos_cw(arg, sn, cs);\n";
     }
-    s += "    fc[" + std::to_string(tm.comp) + "] = fc[" + std::to_string(tm.comp) + "] + v;\n";
-    s += "  }\n";
+    s += "    for (int i = 0; i < M; ++i) {\n";
+    s += "      double amp = " + slot_or_literal(tm.a_slot, tm.a) + ";\n";
+    if (pwc && tm.seg_a_slot >= 0)
+      s += "      amp = p[" + std::to_string(tm.seg_a_slot) + " + seg[i]];\n";
+    const bool is_cos = tm.kind == MSS_TERM_COS || tm.kind == MSS_TERM_PWC_COS;
+    s += std::string("      const double v = amp") + (constant ? "" : is_cos ? " * cs[i]" : " * sn[i]") +
+         ";\n";
+    s += "      f[i][" + comp + "] = ";
+    s += (cond.empty() ? "" : "!on[i] ? f[i][" + comp + "] : ") + std::string("f[i][") + comp +
+         "] + v;\n    }\n  }\n";
   }
-  s += "  f[0] = fc[0];\n  f[1] = fc[1];\n  f[2] = fc[2];\n  f[3] = fc[3];\n}\n";
+  s += "}\n";
   return s;
 }
 

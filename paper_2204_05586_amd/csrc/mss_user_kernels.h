@@ -14,23 +14,31 @@
 #include "mss_device.h"
 #include "mss_work_device.h"
 
+#ifndef MSS_TERMS_FIELD
 __device__ void mss_user_field(double t, const double* params, double* field);
+#endif
 
 struct MssUserField {};
 
-// Found by argument-dependent lookup from the interval operator's templates:
-// nothing of a user's field is known to be constant, and every time is a
-// call of its own.
+// Found by argument-dependent lookup from the interval operator's templates.
+// Nothing is set apart as constant: the compiler moves what does not depend
+// on time out of the loops by itself.
 template <int C>
 __device__ __forceinline__ void field_constant(const MssUserField&, const double* __restrict__,
                                                double (&fc)[C]) {
 #pragma unroll
   for (int j = 0; j < C; ++j) fc[j] = 0.0;
 }
+
+// The field at M times: a generated program takes them all at once, a
+// user's function is called for each.
 template <int C, int M>
 __device__ __forceinline__ void field_at(const MssUserField&, const double* __restrict__ params,
                                          const double (&)[C], const double (&t)[M],
                                          double (&f)[M][C], int = -1) {
+#ifdef MSS_TERMS_FIELD
+  mss_terms_field(t, params, f);
+#else
 #pragma unroll
   for (int i = 0; i < M; ++i) {
     f[i][0] = 0.0;
@@ -39,13 +47,14 @@ __device__ __forceinline__ void field_at(const MssUserField&, const double* __re
     f[i][3] = 0.0;
     mss_user_field(t[i], params, f[i]);
   }
+#endif
 }
 
-extern "C" __global__ void __launch_bounds__(256) mss_user_integrate_2(const mss::IntervalGrid g) {
+extern "C" __global__ void __launch_bounds__(256, 2) mss_user_integrate_2(const mss::IntervalGrid g) {
   mss::integrate_lanes<2>(MssUserField{}, g);
 }
 
-extern "C" __global__ void __launch_bounds__(256) mss_user_integrate_3(const mss::IntervalGrid g) {
+extern "C" __global__ void __launch_bounds__(256, 2) mss_user_integrate_3(const mss::IntervalGrid g) {
   mss::integrate_lanes<3>(MssUserField{}, g);
 }
 
@@ -57,7 +66,7 @@ struct MssUserSource {
   }
 };
 
-extern "C" __global__ void __launch_bounds__(256) mss_user_work_integrate(
+extern "C" __global__ void __launch_bounds__(256, 2) mss_user_work_integrate(
     const mss::IntegrateWorkArgs A) {
   mss::work_integrate_loop(A, MssUserSource{});
 }
