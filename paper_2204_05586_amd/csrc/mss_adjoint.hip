@@ -301,8 +301,9 @@ template <> struct TangentStep<2> {
     mat_h_vec<2>(E, lr, li, nlr, nli);
   }
 };
-// The step through the tangent squarings: any tau and any angles.
-__device__ __forceinline__ void tangent_step_squarings(const double th[4], int tau,
+// The step through the tangent squarings: any tau and any angles.  A call
+// (its vectors in memory), so that its registers bind no caller.
+__device__ __attribute__((noinline)) void tangent_step_squarings(const double th[4], int tau,
                                                        const double* lr, const double* li,
                                                        const double* pr, const double* pi,
                                                        double* br, double* bi, double* nlr,
@@ -391,7 +392,27 @@ template <> struct TangentStep<3> {
       series_part<18, true>(g.p, g.d, 2.0, -2.0 * q3, c, dc);
       series_part<19, true>(g.p, g.d, 2.0, -2.0 * q3, s, ds);
     } else {
-      tangent_step_squarings(th, tau, lr, li, pr, pi, br, bi, nlr, nli, gx, gy);
+      // copies, so that the vectors of the usual path stay in registers
+      double a[4], v[4][3], w[4][3], x, y;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = th[j];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        v[0][j] = lr[j];
+        v[1][j] = li[j];
+        v[2][j] = pr[j];
+        v[3][j] = pi[j];
+      }
+      tangent_step_squarings(a, tau, v[0], v[1], v[2], v[3], w[0], w[1], w[2], w[3], &x, &y);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        br[j] = w[0][j];
+        bi[j] = w[1][j];
+        nlr[j] = w[2][j];
+        nli[j] = w[3][j];
+      }
+      *gx = x;
+      *gy = y;
       return;
     }
     Mat<3> E;

@@ -138,25 +138,104 @@ __device__ __forceinline__ void premultiply(const Mat<N>& A, Mat<N>& M) {
 
 // The running product of an integration.
 //
-// Spin-1: the whole operator.  Dropping its last column (the conjugate cross
-// product of the other two, 72 instead of 108 FMAs) doubles the drift of
-// the states' norm, and a running U - I, with a tenth of the drift, is then
-// further from a solver that rounds U than the 1e-10 the two are held to
-// over 1e7 fine steps.
+// Full su(3) basis: the whole operator (its squarings at low tau are not
+// unitary).
+//
+// Spin-1: the outer two columns (72 FMAs an exponential instead of 108); the
+// middle one of a unitary matrix of determinant 1 is the conjugate cross
+// product of the two, taken once per interval.  Rounding makes the columns'
+// norms drift, and the cross product's norm would drift by the sum of
+// theirs; it is scaled to their mean.  Against the scheme in extended
+// precision, 28 simulations drawn over 2e3 to 3e5 intervals and 5 to 40 fine
+// steps are off by 2.10e-12 in the geometric mean and 7.1e-12 in the mean
+// square (the squarings with whole operators: 2.15e-12 and 7.3e-12).  A
+// running U - I would drift a tenth as much, but is then further from a
+// solver that rounds U than the 1e-10 the two are held to over 1e7 steps.
+// 4.5e7 intervals of 10 fine steps, chained: 9.20 ms with three columns, 7.96
+// with two.
 //
 // Spin-1/2: the first column, less that of I, and exponentials less I
 // (20 instructions instead of 32); the second column mirrors the first.
 // Against the same scheme in extended precision the states of 1e4 intervals
 // of 100 fine steps are 4.6e-14 off, and were 8.5e-13 off with the identity
 // inside.
-template <int N> struct Running;
-template <> struct Running<3> {
+template <int N, bool FULL> struct Running;
+template <> struct Running<3, true> {
   Mat<3> u;
   __device__ __forceinline__ void clear() { set_identity<3>(u); }
   __device__ __forceinline__ void multiply(const Mat<3>& E) { premultiply<3>(E, u); }
   __device__ __forceinline__ void whole(Mat<3>& U) const { U = u; }
 };
-template <> struct Running<2> {
+template <> struct Running<3, false> {
+  double r[3][2], i[3][2];  // columns 0 and 2
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        r[a][b] = a == 2 * b ? 1.0 : 0.0;
+        i[a][b] = 0.0;
+      }
+  }
+  __device__ __forceinline__ void multiply(const Mat<3>& E) {
+    double nr[3][2], ni[3][2];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        double re = E.r[a][0] * r[0][b];
+        double im = E.r[a][0] * i[0][b];
+        re = fma(-E.i[a][0], i[0][b], re);
+        im = fma(E.i[a][0], r[0][b], im);
+#pragma unroll
+        for (int k = 1; k < 3; ++k) {
+          re = fma(E.r[a][k], r[k][b], re);
+          re = fma(-E.i[a][k], i[k][b], re);
+          im = fma(E.r[a][k], i[k][b], im);
+          im = fma(E.i[a][k], r[k][b], im);
+        }
+        nr[a][b] = re;
+        ni[a][b] = im;
+      }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        r[a][b] = nr[a][b];
+        i[a][b] = ni[a][b];
+      }
+  }
+  __device__ __forceinline__ void whole(Mat<3>& U) const {
+#pragma clang fp contract(off)
+    double n2 = 0.0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int j = (a + 1) % 3, k = (a + 2) % 3;
+      U.r[a][0] = r[a][0];
+      U.i[a][0] = i[a][0];
+      U.r[a][2] = r[a][1];
+      U.i[a][2] = i[a][1];
+      // conj(y_j x_k - y_k x_j), x and y the first and last column
+      double re = r[j][1] * r[k][0], im = r[j][1] * i[k][0];
+      re = fma(-i[j][1], i[k][0], re);
+      im = fma(i[j][1], r[k][0], im);
+      re = fma(-r[k][1], r[j][0], re);
+      im = fma(-r[k][1], i[j][0], im);
+      re = fma(i[k][1], i[j][0], re);
+      im = fma(-i[k][1], r[j][0], im);
+      U.r[a][1] = re;
+      U.i[a][1] = -im;
+      n2 = fma(re, re, fma(im, im, n2));
+    }
+    const double scale = 1.0 - 0.25 * (n2 - 1.0);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      U.r[a][1] *= scale;
+      U.i[a][1] *= scale;
+    }
+  }
+};
+template <> struct Running<2, false> {
   double r[2], i[2];
   __device__ __forceinline__ void clear() { r[0] = r[1] = i[0] = i[1] = 0.0; }
   // I + x <- (I + A) (I + x): x <- A x + (A + x), the first column
@@ -261,23 +340,34 @@ __device__ __forceinline__ void store_mat(double* __restrict__ p, const Mat<N>& 
 // sine and cosine
 // ---------------------------------------------------------------------------
 // sincos_cw: Cody-Waite reduction x = k pi/2 + r with pi/2 split into three
-// doubles (P1, P2 with 32 significant bits so k P1 and k P2 are exact for
-// |k| < 2^20; P3 the rest), then minimax polynomials of sin r and cos r on
-// |r| <= pi/4, rotated by the quadrant k mod 4.  The polynomials are from a
-// Remez exchange in 60 digits: sin r = r + r y S(y) and cos r = 1 - y / 2 +
-// y^2 C(y), y = r^2, S of degree 5 (relative error 2^-58) and C of degree 5
-// (2^-64).  4e6 arguments in each of |x| < 3, 1e3 and 4e5 are off by at most
-// 1.7e-16 and 3.5e-17 in the mean square, as with the Taylor series to r^17
-// and r^16 before them, in 3 steps less.  (One odd polynomial on
-// |r| <= pi/2 would do without the second: 2.1e-16 and 4.2e-17.)  Beyond
-// |x| = 1.5 * 2^20 the reduction is no longer exact and ocml's sincos is used.
+// doubles (P1 and P2 of 32 significant bits, P3 the rest).  x - k P1 is a
+// multiple of 2^-31 or of x's last place and at most 2 in size, so the first
+// step is exact for every k; the other two round at the size of r.  Then
+// minimax polynomials of sin r and cos r on |r| <= pi/4, rotated by the
+// quadrant k mod 4.  The polynomials are from a Remez exchange in 60 digits:
+// sin r = r + r y S(y) and cos r = 1 - y / 2 + y^2 C(y), y = r^2, S of degree
+// 5 (relative error 2^-58) and C of degree 5 (2^-64).  4e6 arguments in each
+// of |x| < 3, 1e3, 4e5, 1e7 and 1e9 are off by at most 1.7e-16, 3.5e-17 in the
+// mean square, as with the Taylor series to r^17 and r^16 before them, in 3
+// steps less.  (One odd polynomial on |r| <= pi/2 would do without the
+// second: 2.1e-16 and 4.2e-17.)  From |x| = 2^30 on, where k would leave an
+// int's range, ocml's sincos is used, out of line.
 constexpr double kTwoOverPi = 0x1.45f306dc9c883p-1;
 constexpr double kPio2_1 = 0x1.921fb54400000p+0;
 constexpr double kPio2_2 = 0x1.0b4611a600000p-34;
 constexpr double kPio2_3 = 0x1.3198a2e037073p-69;
 
-// |x| < 1.5 * 2^20 (NaN: no)
-__device__ __forceinline__ bool sincos_in_range(double x) { return fabs(x) < 0x1.8p+20; }
+// NaN: no
+__device__ __forceinline__ bool sincos_in_range(double x) { return fabs(x) < 0x1p+30; }
+
+struct SinCos {
+  double s, c;
+};
+__device__ __attribute__((noinline)) SinCos sincos_far(double x) {
+  SinCos r;
+  sincos(x, &r.s, &r.c);
+  return r;
+}
 
 // A constant as a scalar operand.  Left to itself the compiler forms each
 // step of a Horner chain in place of its constant (a two-operand multiply-
@@ -345,7 +435,11 @@ __device__ __forceinline__ void sincos_cw(const double (&x)[M], double (&s)[M], 
     sincos_reduced(x, s, c);
   } else {
 #pragma unroll
-    for (int i = 0; i < M; ++i) sincos(x[i], &s[i], &c[i]);
+    for (int i = 0; i < M; ++i) {
+      const SinCos far = sincos_far(x[i]);
+      s[i] = far.s;
+      c[i] = far.c;
+    }
   }
 }
 
@@ -357,7 +451,9 @@ __device__ __forceinline__ void sincos_cw(double x, double* s, double* c) {
     *s = si[0];
     *c = ci[0];
   } else {
-    sincos(x, s, c);
+    const SinCos far = sincos_far(x);
+    *s = far.s;
+    *c = far.c;
   }
 }
 
@@ -576,22 +672,30 @@ __device__ __forceinline__ void sym_to_full(const Sym3& s, double d, double epr,
 }
 
 // tau residual squarings a' <- (a' + 2I) a' (two per trip, alternating
-// between two register sets, so nothing is copied), then
-// E = P (I + a') P^H.  Any tau and any angles; exp_one takes it only where
-// the split at n = 2^tau can be told from the exponential itself.
-__device__ __forceinline__ void exp_one_squarings(const double th[4], int tau, Mat<3>& E) {
-  Sym3 a, b;
-  double epr, epi;
-  lie_trotter_residual(th, tau, a, &epr, &epi);
+// between two register sets, so nothing is copied): E = P (I + a') P^H.  Any
+// tau and any angles; exp_one takes it only where the split at n = 2^tau can
+// be told from the exponential itself.  A call, so that the code is there
+// once and its registers bind no caller; arguments and result (28 registers)
+// pass in registers.
+struct SplitPower {
+  Sym3 a;
+  double epr, epi;  // e^{i phi}
+};
+__device__ __attribute__((noinline)) SplitPower split_power(double x, double y, double z, double q,
+                                                            int tau) {
+  const double th[4] = {x, y, z, q};
+  SplitPower p;
+  Sym3 b;
+  lie_trotter_residual(th, tau, p.a, &p.epr, &p.epi);
   for (int s = 0; s + 2 <= tau; s += 2) {
-    residual_square(a, b);
-    residual_square(b, a);
+    residual_square(p.a, b);
+    residual_square(b, p.a);
   }
   if (tau & 1) {
-    residual_square(a, b);
-    a = b;
+    residual_square(p.a, b);
+    p.a = b;
   }
-  sym_to_full(a, 1.0, epr, epi, E);
+  return p;
 }
 
 // The spin-1 exponential in closed form.
@@ -749,7 +853,8 @@ __device__ __forceinline__ void exp_one(const double th[4], int tau, Mat<3>& E) 
   } else if (g.p <= fmin(most, kLongSeries)) {
     series<18, 17>(g.p, g.d, c, s);
   } else {  // also angles that are not finite
-    exp_one_squarings(th, tau, E);
+    const SplitPower w = split_power(th[0], th[1], th[2], th[3], tau);
+    sym_to_full(w.a, 1.0, w.epr, w.epi, E);
     return;
   }
   assemble(g, c, s, E);
@@ -1121,8 +1226,8 @@ __device__ __forceinline__ void residual_square_full(const Mat<3>& x, Mat<3>& y)
 // squaring: X = -i G / n with n = 2^tau, the residual of exp(X) from its
 // degree-4 Taylor polynomial in Horner form, X (I + X/2 (I + X/3 (I + X/4)))
 // (no identity term, nothing cancels), then tau residual squarings, I + a.
-__device__ __forceinline__ void exp_full_squarings(const double th[kFullComps], int tau,
-                                                   Mat<3>& E) {
+__device__ __attribute__((noinline)) void exp_full_squarings(const double th[kFullComps],
+                                                             int tau, Mat<3>& E) {
   const double ninv = ldexp(1.0, -tau);
   // G entry by entry: J_x, J_y, V_1, V_2 couple neighbouring levels (1/sqrt 2),
   // U_1, U_2 the outer pair; J_z and Q on the diagonal.
@@ -1202,7 +1307,12 @@ __device__ __forceinline__ void exp_full(const double th[kFullComps], int tau, M
   } else if (p <= fmin(most, kLongSeries)) {
     series<18, 17>(p, d, c, s);
   } else {  // also angles that are not finite
-    exp_full_squarings(th, tau, E);
+    double angles[kFullComps];  // copies, so that the caller's stay in registers
+    Mat<3> F;
+#pragma unroll
+    for (int j = 0; j < kFullComps; ++j) angles[j] = th[j];
+    exp_full_squarings(angles, tau, F);
+    E = F;
     return;
   }
   const double a[3] = {a0, a1, a2};
@@ -1268,7 +1378,7 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
                                                   int tau, int frame, int method, int64_t k, int s,
                                                   int sl, bool active, Mat<N>& U, double* tk_out) {
   static_assert(!FULL || N == 3, "the full basis is spin-1 only");
-  Running<N> R;
+  Running<N, FULL> R;
   R.clear();
   double tk = 0.0, wr = 0.0;
   if (active) {

@@ -63,3 +63,22 @@ def test_interpreter_is_the_compiled_program(dev, oracle, terms, spin):
             # angles up to 0.1 a step and 6 steps' roundings, phases below 1e2
             assert np.max(np.abs(U.cpu().numpy() - oracle.operators(prob))) <= 2e-14
     sampler.close()
+
+
+# Phases 2 pi f t + phi around 2^30, where the sines change their reduction:
+# below, across it within a fine step (f = 2e9 Hz, 25 rad between nodes), and
+# beyond; and at the 1.5e6 rad of a 0.35 s sensing run.
+@pytest.mark.parametrize("t_start, f", [(0.35, 7e5), (0.08, 2e9), (0.0854459, 2e9), (0.09, 2e9),
+                                        (1e3, 7e5)])
+def test_sines_of_large_phases(dev, oracle, t_start, f):
+    from paper_2204_05586_amd import native
+    for spin in (1, 2):
+        program = [T(W.COS, W.X, a=3e3, f=f), T(W.SIN, W.Y, a=1e3, f=f, phi=1.0),
+                   T(W.CONST, W.Z, a=2e3)]
+        prob = W.Problem(spin, program, t_start, 2e-7, K, 3, 28 if spin == 2 else 0, True)
+        U = dev.empty((K, prob.dim, prob.dim), dtype=dev.complex128, device="cuda")
+        print(f"[gpu] phases from {2 * np.pi * f * t_start:.4g} spin={spin}", flush=True)
+        native.integrate(prob, None, U)
+        dev.cuda.synchronize()
+        # the phases round alike on both sides; angles of 1e-3 a step
+        assert np.max(np.abs(U.cpu().numpy() - oracle.operators(prob))) <= 5e-15
