@@ -984,6 +984,14 @@ mss_status mss_adjoint_plan_create(int32_t n, const mss_problem* problems, const
   P->scan_off.assign(n, 0);
   size_t scan = 0;
   int64_t waves = 0, pend = 0;
+  // the forward pass's lane-slices, planned on all its intervals
+  int64_t k_all = 0;
+  int32_t l_min = problems[0].n_fine;
+  for (int i = 0; i < n; ++i) {
+    k_all += problems[i].n_samples;
+    l_min = std::min(l_min, problems[i].n_fine);
+  }
+  const int sl = api_ilog2(api_plan_slices(k_all, l_min, api_device_cu_count()));
   for (int i = 0; i < n; ++i) {
     const mss_problem& q = problems[i];
     const int N = q.spin_twice + 1;
@@ -995,7 +1003,7 @@ mss_status mss_adjoint_plan_create(int32_t n, const mss_problem* problems, const
     pend = std::max<int64_t>(pend, P->param_off[i] + q.n_params);
     P->scan_off[i] = scan;
     scan += scan_scratch_bytes(N, q.n_samples);
-    P->fwd.add(q, 0, 0, q.n_samples, true);
+    P->fwd.add(q, sl, 0, q.n_samples, true);
     P->bwd.add(q, 0, 0, 0, true);
     AdjDesc a;
     memset(&a, 0, sizeof a);

@@ -90,17 +90,25 @@ int ilog2(int x) {
   return l;
 }
 
-// Lane-slice count: minimise (waves per SIMD, rounded up) x (fine steps per
-// lane, rounded up); ties go to fewer slices.
+// Lane-slice count: minimise the work of the fullest SIMD, its waves times
+// what each does: the fine steps of a lane, the frame's set-up and exit
+// (about one step) and the combination of the slices (0.2 of a step a
+// level).  A SIMD that holds one wave does not reach its issue rate: it
+// takes as long as 1.25 waves' work.  Beyond four waves to a SIMD the rounds
+// overlap and half a wave is left over on average.  Ties go to fewer slices.
+// Over nine shapes (spin-1/2 and spin-1, 1e3 to 1e6 intervals, 10 to 100
+// fine steps) the choice is within 4 % of the best of 1 to 16 slices (spin-1
+// 1e6 x 10: one slice 159 us, two 172; 5e4 x 20 in the lab frame: one 33.9,
+// two 27.5).
 int plan_slices(int64_t K, int32_t L, int cu) {
-  const int64_t simds = (int64_t)cu * 4;
+  const double simds = (double)cu * 4;
   int best = 1;
   double best_cost = 1e300;
   for (int S = 1; S <= 64 && S <= L; S <<= 1) {
-    const int64_t waves = (K * S + 63) / 64;
-    const int64_t per_simd = (waves + simds - 1) / simds;
-    const int64_t steps = (L + S - 1) / S;
-    const double cost = (double)per_simd * ((double)steps + 0.1 * ilog2(S));
+    const double per_simd = (double)((K * S + 63) / 64) / simds;
+    const double waves = per_simd <= 1.0 ? 1.25 : per_simd <= 4.0 ? ceil(per_simd) : per_simd + 0.5;
+    const double steps = (double)((L + S - 1) / S);
+    const double cost = waves * (steps + 1.0 + 0.2 * ilog2(S));
     if (cost < best_cost * (1.0 - 1e-9)) {
       best_cost = cost;
       best = S;
@@ -212,10 +220,8 @@ mss_status api_validate_terms(int spin_twice, const mss_term* terms, int n_terms
 
 namespace {
 
-mss_status resolve_launch(const mss_problem* p, const mss_launch* in, int* slices, int* block,
-                          bool* given) {
+mss_status resolve_launch(const mss_problem* p, const mss_launch* in, int* slices, int* block) {
   int S = in ? in->slices : 0;
-  if (given) *given = S != 0;
   int B = in ? in->block : 0;
   const int cu = device_cu_count();
   if (S == 0) S = plan_slices(p->n_samples, p->n_fine, cu);
@@ -245,37 +251,9 @@ mss_status resolve_launch(const mss_problem* p, const mss_launch* in, int* slice
 }  // namespace
 
 namespace mss {
-mss_status api_resolve_launch(const mss_problem* p, const mss_launch* in, int* slices, int* block,
-                              bool* given) {
-  return resolve_launch(p, in, slices, block, given);
-}
-
-void api_plan_lane_segments(IntervalGrid& g, int S0, bool given, int64_t slots) {
-  const int64_t K = g.K;
-  const int L = g.L;
-  g.n_seg = 1;
-  g.seg_sl[0] = g.seg_sl[1] = ilog2(S0);
-  g.seg_k0[0] = 0;
-  g.seg_w0[0] = 0;
-  g.seg_k0[1] = K;
-  g.seg_w0[1] = 0;
-  if (given || slots <= 0) return;
-  const int64_t per0 = 64 / S0;
-  const int64_t W0 = (K + per0 - 1) / per0;
-  if (W0 <= slots) return;  // at most one round: the slice count already fills it
-  const int64_t full = (W0 / slots) * slots;
-  const int64_t k_main = full * per0;
-  const int64_t rest = K - k_main;
-  if (rest <= 0) return;
-  // the leftover intervals, sliced as finely as one round of waves allows
-  int S1 = S0;
-  const int cap = L < 64 ? L : 64;
-  while (S1 * 2 <= cap && (rest * S1 * 2 + 63) / 64 <= slots) S1 *= 2;
-  if ((L + S1 - 1) / S1 >= (L + S0 - 1) / S0) return;  // no shorter final round
-  g.n_seg = 2;
-  g.seg_sl[1] = ilog2(S1);
-  g.seg_k0[1] = k_main;
-  g.seg_w0[1] = full;
+mss_status api_resolve_launch(const mss_problem* p, const mss_launch* in, int* slices,
+                              int* block) {
+  return resolve_launch(p, in, slices, block);
 }
 
 bool same_phase(const mss_term& a, const mss_term& b) {
@@ -308,12 +286,6 @@ int program_order(const mss_term* terms, int n, mss_term* out) {
   for (int i = 0; i < n; ++i)
     if (!((varying >> terms[i].comp) & 1)) out[k++] = terms[i];
   return n_varying;
-}
-
-int64_t api_grid_waves(const IntervalGrid& g) {
-  const int j = g.n_seg - 1;
-  const int64_t per = 64 >> g.seg_sl[j];
-  return g.seg_w0[j] + (g.K - g.seg_k0[j] + per - 1) / per;
 }
 }  // namespace mss
 
@@ -408,7 +380,7 @@ mss_status mss_plan_launch(const mss_problem* p, mss_launch* out) {
   if (s != MSS_OK) return s;
   if (!out) return api_fail(MSS_E_INVALID, "out is NULL");
   int S, B;
-  if ((s = resolve_launch(p, nullptr, &S, &B, nullptr)) != MSS_OK) return s;
+  if ((s = resolve_launch(p, nullptr, &S, &B)) != MSS_OK) return s;
   out->slices = S;
   out->block = B;
   return api_ok();
@@ -440,8 +412,7 @@ mss_status mss_integrate(const mss_problem* p, const double* params, double* U, 
   if (!U) return api_fail(MSS_E_INVALID, "U is NULL");
   if (p->n_params > 0 && !params) return api_fail(MSS_E_INVALID, "params is NULL but n_params > 0");
   int S, B;
-  bool given = false;
-  if ((s = resolve_launch(p, launch, &S, &B, &given)) != MSS_OK) return s;
+  if ((s = resolve_launch(p, launch, &S, &B)) != MSS_OK) return s;
   IntegrateArgs a;
   memset(&a, 0, sizeof a);
   a.fp.n_terms = p->n_terms;
@@ -458,7 +429,7 @@ mss_status mss_integrate(const mss_problem* p, const double* params, double* U, 
   a.g.frame = p->rotating_frame;
   a.g.method = p->method;
   a.g.full = api_full_basis(p) ? 1 : 0;
-  api_plan_lane_segments(a.g, S, given, integrate_slots(p->spin_twice + 1, B));
+  a.g.sl = ilog2(S);
   hipError_t e = launch_integrate(p->spin_twice + 1, a, B, (hipStream_t)stream);
   if (e != hipSuccess) return api_hip_fail(e, "integrate launch");
   return api_ok();

@@ -41,13 +41,8 @@ mss_status api_sampler_check_problem(mss_sampler s, const mss_problem* p);
 int api_device_cu_count();
 int api_plan_slices(int64_t K, int32_t L, int cu);
 int api_ilog2(int x);
-// launch shape (lane-slices per interval, block size) of one simulation;
-// given: whether the caller fixed the slices
-mss_status api_resolve_launch(const mss_problem* p, const mss_launch* in, int* slices, int* block,
-                              bool* given);
-// lane segments of a grid launch with S0 slices (IntervalGrid), given the
-// number of waves that run at once (slots; 0: unknown, one segment)
-void api_plan_lane_segments(IntervalGrid& g, int S0, bool given, int64_t slots);
+// launch shape (lane-slices per interval, block size) of one simulation
+mss_status api_resolve_launch(const mss_problem* p, const mss_launch* in, int* slices, int* block);
 // Whether b, the term after a, takes the same phase 2 pi f t + phi at every
 // time at which either is on, and the same segments: a circular drive's
 // cosine and sine, evaluated once then.
@@ -59,12 +54,6 @@ bool same_phase(const mss_term& a, const mss_term& b);
 // order, so the field is the list's bit for bit.  Returns the count of the
 // first kind.
 int program_order(const mss_term* terms, int n, mss_term* out);
-// waves of a planned grid launch
-int64_t api_grid_waves(const IntervalGrid& g);
-// waves of integrate_kernel<N> in blocks of `block` threads that run at once
-// on the current device (0 if unknown)
-int64_t integrate_slots(int N, int block);
-
 // work-queue integrator of a user sampler's module on the current device
 // (loads the module there on first use); chained: the form that also forms
 // the states (launch_work_chained)

@@ -310,8 +310,7 @@ mss_status mss_sampler_integrate(mss_sampler s, const mss_problem* p, const doub
   if (p->n_params > 0 && !params) return api_fail(MSS_E_INVALID, "params is NULL but n_params > 0");
   if ((st = api_sampler_check_problem(s, p)) != MSS_OK) return st;
   int S, B;
-  bool given = false;
-  if ((st = api_resolve_launch(p, launch, &S, &B, &given)) != MSS_OK) return st;
+  if ((st = api_resolve_launch(p, launch, &S, &B)) != MSS_OK) return st;
   const mss_sampler_s::Module* m = nullptr;
   if ((st = load_on_current(s, &m)) != MSS_OK) return st;
   IntervalGrid g;
@@ -328,12 +327,8 @@ mss_status mss_sampler_integrate(mss_sampler s, const mss_problem* p, const doub
   g.frame = p->rotating_frame;
   g.method = p->method;
   hipFunction_t fn = m->fn[p->spin_twice - 1];
-  int blocks = 0, cu = api_device_cu_count();
-  int64_t slots = 0;
-  if (hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, fn, B, 0) == hipSuccess)
-    slots = (int64_t)blocks * (B / 64) * cu;
-  api_plan_lane_segments(g, S, given, slots);
-  const unsigned grid = (unsigned)((api_grid_waves(g) * 64 + B - 1) / B);
+  g.sl = api_ilog2(S);
+  const unsigned grid = (unsigned)(((p->n_samples << g.sl) + B - 1) / B);
   void* args[] = {&g};
   hipError_t e = hipModuleLaunchKernel(fn, grid, 1, 1, (unsigned)B, 1, 1, 0,
                                        (hipStream_t)stream, args, nullptr);
