@@ -5,9 +5,10 @@
 //   1. forward: the batch integrator (operators kept) and scan (states);
 //   2. seed: loss and the costate lambda_K = e_m psi_final[m] (so that
 //      dloss = 2 Re lambda^H dpsi_final), gradients cleared;
-//   3. costates lambda_k = U_k^H lambda_{k+1} for all k: the segmented scan
-//      run over the reversed, conjugate-transposed operators;
-//   4. one lane per (simulation, interval): replay the interval backward
+//   3. costates lambda_k = U_k^H lambda_{k+1} for all k: the segmented scan,
+//      reading the operators from the end and conjugate-transposed;
+//   4. one lane per (simulation, interval), or several where these leave the
+//      device idle: replay the interval backward
 //      from (psi_{k+1}, lambda_{k+1}) in frame coordinates, recovering the
 //      state before each exponential as E^H psi (E is unitary), take
 //      dloss/dtheta = 2 Re(lambda^H dE/dtheta psi_before) with dE/dtheta
@@ -18,6 +19,7 @@
 //      the output with FP64 atomics.
 // Parameters may be used by x and y terms (any kind); a z or q term with a
 // parameter slot is rejected (MSS_E_UNSUPPORTED).
+#include <math.h>
 #include <string.h>
 
 #include <algorithm>
@@ -454,7 +456,7 @@ constexpr int kAdjointBlock = 256;
 struct AdjDesc {
   double t_start, dt_out, dt;
   int64_t K;
-  int64_t wave_off;            // first wave (64 intervals per wave)
+  int64_t wave_off;            // first wave (64 / S intervals per wave)
   const double* params;
   double* grad;
   const double* psi;           // forward states [K][N]
@@ -473,6 +475,7 @@ struct AdjArgs {
   const mss_term* terms;
   int64_t n_waves;
   int32_t n_sims;
+  int32_t slices_log2;  // lanes per interval
 };
 
 struct GradAcc {
@@ -522,6 +525,8 @@ __device__ __forceinline__ void field_keep(const AdjDesc& s, const mss_term* ter
     for (int j = 0; j < 4; ++j) f[i][j] = 0.0;
   double sn[2] = {0.0, 0.0}, cs[2] = {1.0, 1.0};
   int seg[2] = {-1, -1}, g = 0;
+  double amp[2] = {0.0, 0.0};
+  int amp_slot = -1;  // where amp's segment array starts
   for (int n = 0; n < s.n_terms; ++n) {
     Constant<mss_term>& tm = as_constant(terms)[s.term_off + n];
     // g stays uniform across the wave: it moves on whether or not the term is on
@@ -536,8 +541,7 @@ __device__ __forceinline__ void field_keep(const AdjDesc& s, const mss_term* ter
     }
     const int kind = tm.kind, comp = tm.comp;
     const bool again = (s.same_phase >> n) & 1;
-    const double a = tm.a_slot >= 0 ? as_constant(params)[tm.a_slot] : tm.a;
-    double amp[2] = {a, a};
+    const int from = kind >= MSS_TERM_PWC ? tm.seg_a_slot : -1;
     if (kind >= MSS_TERM_PWC) {
       if (!again) {
         const double t0 = tm.seg_t0, len = tm.seg_len;
@@ -549,13 +553,16 @@ __device__ __forceinline__ void field_keep(const AdjDesc& s, const mss_term* ter
           seg[i] = fl < 0.0 ? 0 : (fl > (double)last ? last : (int)fl);
         }
       }
-      if (tm.seg_a_slot >= 0) {
-        amp[0] = params[tm.seg_a_slot + seg[0]];
-        amp[1] = params[tm.seg_a_slot + seg[1]];
-      }
     } else {
       seg[0] = seg[1] = -1;
     }
+    if (from < 0) {
+      amp[0] = amp[1] = tm.a_slot >= 0 ? as_constant(params)[tm.a_slot] : tm.a;
+    } else if (!again || from != amp_slot) {  // a pair of one phase mostly has one amplitude
+      amp[0] = params[from + seg[0]];
+      amp[1] = params[from + seg[1]];
+    }
+    amp_slot = from;
     double val[2] = {1.0, 1.0}, dphase[2] = {0.0, 0.0};
     if (kind != MSS_TERM_CONST && kind != MSS_TERM_PWC) {
       if (!again) {
@@ -622,39 +629,97 @@ __device__ __forceinline__ void node_grad(const AdjDesc& s, const mss_term* term
   }
 }
 
+// One interval by 2^sl cooperating lanes of a wave, slice `slice` replaying
+// fine steps [slice L / S, (slice + 1) L / S).  With S > 1 every lane first
+// integrates its slice's operator V forward (as the integrator does) and the
+// operators after it, X = V_{S-1} ... V_{slice+1} by a shuffle scan, carry the
+// interval's final state and costate to the end of its slice by X^H: some 40 %
+// more work in all, against S times the lanes.  Every lane of the wave must
+// call this (active: the lane has an interval).
 template <int N>
 __device__ __forceinline__ void adjoint_interval(const AdjArgs& A, const AdjDesc& s, int64_t k,
+                                                 int slice, int sl, bool active,
                                                  KeptTerms& kept) {
   // the list as it stands: no part of it is set apart as constant
   const TableTerms terms{A.terms + s.term_off, s.n_terms, s.n_terms};
   const double none[4] = {0.0, 0.0, 0.0, 0.0};
-  double tk, wr;
-  interval_setup(terms, s.params, none, s.t_start, s.dt_out, k, s.frame, &tk, &wr);  // CF4 only
-  // psi_{k+1}, lambda_{k+1} into frame coordinates: R^H x, R = diag(e^{-i m wr Dt}),
-  // opposite turns of the two outer levels
-  const double* pn = (k + 1 < s.K) ? s.psi + (size_t)(k + 1) * 2 * N : s.psi_final;
-  const double* ln = s.lam_before + (size_t)(s.K - 1 - k) * 2 * N;
+  double tk = 0.0, wr = 0.0;
+  const int l0 = (int)(((int64_t)slice * s.n_fine) >> sl);
+  const int l1 = (int)(((int64_t)(slice + 1) * s.n_fine) >> sl);
   double pr[N], pi[N], lr[N], li[N];
-  double se, ce;
-  sincos_cw((N == 2 ? 0.5 : 1.0) * (wr * s.dt_out), &se, &ce);
 #pragma unroll
-  for (int a = 0; a < N; ++a) {
-    const double sn = a == 0 ? se : (a == N - 1 ? -se : 0.0);
-    const double cs = a == 0 || a == N - 1 ? ce : 1.0;
-    pr[a] = fma(cs, pn[2 * a], -sn * pn[2 * a + 1]);
-    pi[a] = fma(cs, pn[2 * a + 1], sn * pn[2 * a]);
-    lr[a] = fma(cs, ln[2 * a], -sn * ln[2 * a + 1]);
-    li[a] = fma(cs, ln[2 * a + 1], sn * ln[2 * a]);
+  for (int a = 0; a < N; ++a) pr[a] = pi[a] = lr[a] = li[a] = 0.0;
+  NodeRotations rot;
+  rot.c[0] = rot.c[1] = 1.0;  // the lab frame
+  rot.s[0] = rot.s[1] = 0.0;
+  if (active) {
+    interval_setup(terms, s.params, none, s.t_start, s.dt_out, k, s.frame, &tk, &wr);  // CF4 only
+    // psi_{k+1}, lambda_{k+1} into frame coordinates: R^H x, R = diag(e^{-i m wr Dt}),
+    // opposite turns of the two outer levels
+    const double* pn = (k + 1 < s.K) ? s.psi + (size_t)(k + 1) * 2 * N : s.psi_final;
+    const double* ln = s.lam_before + (size_t)(s.K - 1 - k) * 2 * N;
+    double se, ce;
+    sincos_cw((N == 2 ? 0.5 : 1.0) * (wr * s.dt_out), &se, &ce);
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+      const double sn = a == 0 ? se : (a == N - 1 ? -se : 0.0);
+      const double cs = a == 0 || a == N - 1 ? ce : 1.0;
+      pr[a] = fma(cs, pn[2 * a], -sn * pn[2 * a + 1]);
+      pi[a] = fma(cs, pn[2 * a + 1], sn * pn[2 * a]);
+      lr[a] = fma(cs, ln[2 * a], -sn * ln[2 * a + 1]);
+      li[a] = fma(cs, ln[2 * a + 1], sn * ln[2 * a]);
+    }
   }
+  if (sl > 0) {  // uniform across the launch
+    Mat<N> Y;
+    Running<N, false> R;
+    R.clear();
+    if (active) {
+      if (wr != 0.0) rot.start(wr, l0, s.dt);
+#pragma unroll 1
+      for (int l = l0; l < l1; ++l) {
+        double th1[4], th2[4];
+        cf4_angles(terms, s.params, none, tk, l, s.dt, wr, rot, th1, th2);
+        if (wr != 0.0) rot.advance();
+#pragma unroll 1
+        for (int e = 0; e < 2; ++e) {
+          const double th[4] = {e ? th2[0] : th1[0], e ? th2[1] : th1[1], e ? th2[2] : th1[2],
+                                e ? th2[3] : th1[3]};
+          Mat<N> E;
+          Exponentiator<N>::apply(th, s.tau, E);
+          R.multiply(E);
+        }
+      }
+    }
+    R.whole(Y);
+    // Y = V_{S-1} ... V_slice, then X its part after the slice
+    for (int d = 1; d < (1 << sl); d <<= 1) {
+      const Mat<N> o = shfl_down_mat<N>(Y, d);
+      if (slice + d < (1 << sl)) premultiply<N>(o, Y);
+    }
+    Mat<N> X = shfl_down_mat<N>(Y, 1);
+    if (slice + 1 == (1 << sl)) set_identity<N>(X);
+    double yr[N], yi[N];
+    mat_h_vec<N>(X, pr, pi, yr, yi);
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+      pr[a] = yr[a];
+      pi[a] = yi[a];
+    }
+    mat_h_vec<N>(X, lr, li, yr, yi);
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+      lr[a] = yr[a];
+      li[a] = yi[a];
+    }
+  }
+  if (!active) return;
   GradAcc acc[kMaxGradTerms];
 #pragma unroll
   for (int g = 0; g < kMaxGradTerms; ++g) acc[g] = {-1, 0.0, 0.0, 0.0};
   const double wgt[2][2] = {{kWPlus, kWMinus}, {kWMinus, kWPlus}};  // [node][exponential]
-  NodeRotations rot;
-  rot.c[0] = rot.c[1] = 1.0;  // the lab frame
-  rot.s[0] = rot.s[1] = 0.0;
-  if (wr != 0.0) rot.start(wr, s.n_fine - 1, s.dt);
-  for (int l = s.n_fine - 1; l >= 0; --l) {
+  if (wr != 0.0) rot.start(wr, l1 - 1, s.dt);
+  for (int l = l1 - 1; l >= l0; --l) {
     const double t[2] = {tk + node_offset(0, l, s.dt), tk + node_offset(1, l, s.dt)};
     double f[2][4], w[2][4], th[2][4];
     field_keep(s, A.terms, t, kept, f);
@@ -711,10 +776,11 @@ __global__ void __launch_bounds__(kAdjointBlock, 2) adjoint_kernel(const AdjArgs
     else hi = mid - 1;
   }
   const AdjDesc s = load_constant(A.sims + lo);
-  const int64_t k = (wave - s.wave_off) * 64 + lane;
-  if (k >= s.K) return;
-  if (s.spin_twice == 2) adjoint_interval<3>(A, s, k, kept);
-  else adjoint_interval<2>(A, s, k, kept);
+  const int sl = A.slices_log2;
+  const int64_t k = ((wave - s.wave_off) << (6 - sl)) + (lane >> sl);
+  const int slice = lane & ((1 << sl) - 1);
+  if (s.spin_twice == 2) adjoint_interval<3>(A, s, k, slice, sl, k < s.K, kept);
+  else adjoint_interval<2>(A, s, k, slice, sl, k < s.K, kept);
 }
 
 // loss_i and the seed costate lambda_K = e_m psi_final[m]; gradients cleared.
@@ -745,38 +811,6 @@ __global__ void adjoint_seed_kernel(const SeedArgs A) {
   }
 }
 
-// W[j] = U[K - 1 - j]^H within each simulation (operators packed by op_off).
-struct ReverseArgs {
-  const AdjDesc* sims;
-  const int64_t* op_off;    // complex offsets per simulation (n + 1)
-  const int64_t* mat_off;   // matrix-count prefix per simulation (n + 1)
-  const double* U;
-  double* W;
-  int64_t n_mats;
-  int32_t n_sims;
-};
-
-__global__ void adjoint_reverse_kernel(const ReverseArgs A) {
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= A.n_mats) return;
-  int lo = 0, hi = A.n_sims - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (A.mat_off[mid] <= gid) lo = mid;
-    else hi = mid - 1;
-  }
-  const int64_t j = gid - A.mat_off[lo];
-  const int64_t K = A.sims[lo].K;
-  const int N = A.sims[lo].spin_twice + 1;
-  const double* src = A.U + 2 * (A.op_off[lo] + (K - 1 - j) * N * N);
-  double* dst = A.W + 2 * (A.op_off[lo] + j * N * N);
-  for (int a = 0; a < N; ++a)
-    for (int b = 0; b < N; ++b) {
-      dst[2 * (a * N + b)] = src[2 * (b * N + a)];
-      dst[2 * (a * N + b) + 1] = -src[2 * (b * N + a) + 1];
-    }
-}
-
 }  // namespace mss
 
 using namespace mss;
@@ -789,22 +823,22 @@ struct mss_adjoint_plan {
   int32_t m = 0;
   std::vector<mss_problem> probs;
   std::vector<std::vector<mss_term>> term_store;
-  std::vector<int64_t> psi0_off, state_off, op_off, mat_off, param_off;
+  std::vector<int64_t> psi0_off, state_off, op_off, param_off;
   std::vector<size_t> scan_off;
-  int64_t n_params_total = 0, n_mats = 0, n_waves = 0;
+  int64_t n_params_total = 0, n_waves = 0;
   size_t scan_bytes = 0;
   WorkSet fwd, bwd;
   std::vector<AdjDesc> adj;
   std::vector<mss_term> terms;
   // workspace layout (bytes)
-  size_t o_counter = 0, o_U = 0, o_W = 0, o_psi = 0, o_fin = 0, o_lamK = 0, o_lam = 0,
+  size_t o_counter = 0, o_U = 0, o_psi = 0, o_fin = 0, o_lamK = 0, o_lam = 0,
          o_lam0 = 0, o_scan = 0, ws_bytes = 0;
   int grid_blocks = 0;
+  int adj_sl = 0;  // log2 of the backward kernel's lanes per interval
   // device descriptors: [fwd image | bwd image | adj | terms | offsets]
   void* desc = nullptr;
   std::vector<char> image;
-  size_t f_sims = 0, f_terms = 0, b_sims = 0, b_terms = 0, a_sims = 0, a_terms = 0, a_psi0 = 0,
-         a_op = 0, a_mat = 0;
+  size_t f_sims = 0, f_terms = 0, b_sims = 0, b_terms = 0, a_sims = 0, a_terms = 0, a_psi0 = 0;
   std::vector<size_t> f_red, f_app, b_red, b_app;
   size_t f_base = 0, b_base = 0;
   DevWork dfwd, dbwd;
@@ -826,6 +860,34 @@ void release(mss_adjoint_plan* P) {
   delete P;
 }
 
+// Lanes per interval of the backward kernel: the work of the fullest SIMD,
+// its waves (1.25 for a lone one, which leaves issue slots idle) times what
+// each does, in fine steps of the replay.  More than one lane integrates its
+// slice forward first (0.45 of a replayed step each) and scans (half a step
+// a level); set-up and flush are about a step.  With one lane per interval in
+// both passes, 4 instances of 1,000 intervals of 100 fine steps took 4.4 ms
+// and take 0.2 (64: 4.5 and 0.8; 256: 2.1 and 1.95, one lane still).
+int plan_adjoint_slices(int n, const mss_problem* problems, int32_t l_min, int cu) {
+  int best = 1;
+  double best_cost = 1e300;
+  for (int S = 1; S <= 16 && S <= l_min; S <<= 1) {
+    int64_t waves = 0;
+    double steps = 0.0;
+    for (int i = 0; i < n; ++i) {
+      waves += (problems[i].n_samples + 64 / S - 1) / (64 / S);
+      steps = std::max(steps, (double)((problems[i].n_fine + S - 1) / S));
+    }
+    const double per_simd = (double)waves / (4.0 * cu);
+    const double w = per_simd <= 1.0 ? 1.25 : per_simd <= 4.0 ? ceil(per_simd) : per_simd + 0.5;
+    const double each = S == 1 ? steps + 1.0 : 1.45 * steps + 2.0 + 0.5 * api_ilog2(S);
+    if (w * each < best_cost * (1.0 - 1e-9)) {
+      best_cost = w * each;
+      best = S;
+    }
+  }
+  return best;
+}
+
 void pack_all(mss_adjoint_plan* P) {
   std::vector<char>& img = P->image;
   size_t off = 0;
@@ -839,16 +901,12 @@ void pack_all(mss_adjoint_plan* P) {
   P->a_sims = reserve(P->adj.size() * sizeof(AdjDesc));
   P->a_terms = reserve(std::max<size_t>(1, P->terms.size()) * sizeof(mss_term));
   P->a_psi0 = reserve(P->psi0_off.size() * 8);
-  P->a_op = reserve(P->op_off.size() * 8);
-  P->a_mat = reserve(P->mat_off.size() * 8);
   img.assign(off, 0);
   P->fwd.pack(img.data() + P->f_base, &P->f_sims, &P->f_terms, &P->f_red, &P->f_app);
   P->bwd.pack(img.data() + P->b_base, &P->b_sims, &P->b_terms, &P->b_red, &P->b_app);
   memcpy(img.data() + P->a_sims, P->adj.data(), P->adj.size() * sizeof(AdjDesc));
   if (!P->terms.empty()) memcpy(img.data() + P->a_terms, P->terms.data(), P->terms.size() * sizeof(mss_term));
   memcpy(img.data() + P->a_psi0, P->psi0_off.data(), P->psi0_off.size() * 8);
-  memcpy(img.data() + P->a_op, P->op_off.data(), P->op_off.size() * 8);
-  memcpy(img.data() + P->a_mat, P->mat_off.data(), P->mat_off.size() * 8);
 }
 
 template <class T>
@@ -868,7 +926,6 @@ mss_status bind(mss_adjoint_plan* P, const double* params, const double* psi0, d
   }
   char* w = (char*)ws;
   double* U = (double*)(w + P->o_U);
-  double* W = (double*)(w + P->o_W);
   double* psi = (double*)(w + P->o_psi);
   double* fin = (double*)(w + P->o_fin);
   double* lamK = (double*)(w + P->o_lamK);
@@ -887,7 +944,7 @@ mss_status bind(mss_adjoint_plan* P, const double* params, const double* psi0, d
     b.psi0 = lamK + 2 * P->psi0_off[i];
     b.psi = lam + 2 * P->state_off[i];
     b.psi_final = lam0 + 2 * P->psi0_off[i];
-    b.U = W + 2 * P->op_off[i];
+    b.U = f.U;  // scanned from the end, conjugate-transposed (DevWork::reversed)
     b.scan_ws = f.scan_ws;
     AdjDesc& a = P->adj[i];
     a.params = f.params;
@@ -902,6 +959,7 @@ mss_status bind(mss_adjoint_plan* P, const double* params, const double* psi0, d
   const char* d = (const char*)P->desc;
   P->dfwd = device_view(P->fwd, d + P->f_base, P->f_sims, P->f_terms, P->f_red, P->f_app);
   P->dbwd = device_view(P->bwd, d + P->b_base, P->b_sims, P->b_terms, P->b_red, P->b_app);
+  P->dbwd.reversed = true;
   for (int i = 0; i < 5; ++i) P->bound[i] = key[i];
   P->have_bind = true;
   return MSS_OK;
@@ -979,7 +1037,6 @@ mss_status mss_adjoint_plan_create(int32_t n, const mss_problem* problems, const
   P->psi0_off.assign(n + 1, 0);
   P->state_off.assign(n + 1, 0);
   P->op_off.assign(n + 1, 0);
-  P->mat_off.assign(n + 1, 0);
   P->param_off.assign(n, 0);
   P->scan_off.assign(n, 0);
   size_t scan = 0;
@@ -992,13 +1049,13 @@ mss_status mss_adjoint_plan_create(int32_t n, const mss_problem* problems, const
     l_min = std::min(l_min, problems[i].n_fine);
   }
   const int sl = api_ilog2(api_plan_slices(k_all, l_min, api_device_cu_count()));
+  P->adj_sl = api_ilog2(plan_adjoint_slices(n, problems, l_min, api_device_cu_count()));
   for (int i = 0; i < n; ++i) {
     const mss_problem& q = problems[i];
     const int N = q.spin_twice + 1;
     P->psi0_off[i + 1] = P->psi0_off[i] + N;
     P->state_off[i + 1] = P->state_off[i] + q.n_samples * N;
     P->op_off[i + 1] = P->op_off[i] + q.n_samples * N * N;
-    P->mat_off[i + 1] = P->mat_off[i] + q.n_samples;
     P->param_off[i] = q.n_params > 0 ? param_off[i] : 0;
     pend = std::max<int64_t>(pend, P->param_off[i] + q.n_params);
     P->scan_off[i] = scan;
@@ -1012,7 +1069,7 @@ mss_status mss_adjoint_plan_create(int32_t n, const mss_problem* problems, const
     a.dt = q.dt_out / (double)q.n_fine;
     a.K = q.n_samples;
     a.wave_off = waves;
-    waves += (q.n_samples + 63) / 64;
+    waves += (q.n_samples + (64 >> P->adj_sl) - 1) / (64 >> P->adj_sl);
     a.spin_twice = q.spin_twice;
     a.n_terms = q.n_terms;
     a.term_off = (int32_t)P->terms.size();
@@ -1034,7 +1091,6 @@ mss_status mss_adjoint_plan_create(int32_t n, const mss_problem* problems, const
   P->fwd.finalize();
   P->bwd.finalize();
   P->n_params_total = pend;
-  P->n_mats = P->mat_off[n];
   P->n_waves = waves;
   P->scan_bytes = scan;
   // workspace layout
@@ -1046,7 +1102,6 @@ mss_status mss_adjoint_plan_create(int32_t n, const mss_problem* problems, const
   };
   P->o_counter = take(256);
   P->o_U = take((size_t)P->op_off[n] * 16);
-  P->o_W = take((size_t)P->op_off[n] * 16);
   P->o_psi = take((size_t)P->state_off[n] * 16);
   P->o_fin = take((size_t)P->psi0_off[n] * 16);
   P->o_lamK = take((size_t)P->psi0_off[n] * 16);
@@ -1105,16 +1160,12 @@ mss_status mss_adjoint_run(mss_adjoint_plan* P, const double* params, const doub
                 P->n_params_total, P->n, P->m};
     const int64_t n = std::max<int64_t>(P->n_params_total, P->n);
     hipLaunchKernelGGL(adjoint_seed_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, sa);
-    ReverseArgs ra{(const AdjDesc*)(d + P->a_sims), (const int64_t*)(d + P->a_op),
-                   (const int64_t*)(d + P->a_mat), (const double*)(w + P->o_U),
-                   (double*)(w + P->o_W), P->n_mats, P->n};
-    hipLaunchKernelGGL(adjoint_reverse_kernel, dim3((unsigned)((P->n_mats + 255) / 256)), dim3(256),
-                       0, st, ra);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = launch_work_scan(P->dbwd, st);
   if (e == hipSuccess) {
-    AdjArgs aa{(const AdjDesc*)(d + P->a_sims), (const mss_term*)(d + P->a_terms), P->n_waves, P->n};
+    AdjArgs aa{(const AdjDesc*)(d + P->a_sims), (const mss_term*)(d + P->a_terms), P->n_waves, P->n,
+               P->adj_sl};
     hipLaunchKernelGGL(adjoint_kernel, dim3((unsigned)((P->n_waves + 3) / 4)),
                        dim3(kAdjointBlock), 0, st, aa);
     e = hipGetLastError();

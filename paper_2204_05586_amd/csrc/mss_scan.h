@@ -33,21 +33,42 @@ __device__ __forceinline__ void project_spin(const double* vr, const double* vi,
   j3[2] = jz;
 }
 
+// Element idx of a sequence of n matrices at M; with REV, of the sequence
+// reversed and conjugate-transposed: M[n - 1 - idx]^H (the costates of an
+// adjoint go through the operators that way).
+template <int N, bool REV>
+__device__ __forceinline__ void load_element(const double* __restrict__ M, int64_t n, int64_t idx,
+                                             Mat<N>& X) {
+  if constexpr (REV) {
+    Mat<N> Y;
+    load_mat<N>(M + (size_t)(n - 1 - idx) * 2 * N * N, Y);
+#pragma unroll
+    for (int a = 0; a < N; ++a)
+#pragma unroll
+      for (int b = 0; b < N; ++b) {
+        X.r[a][b] = Y.r[b][a];
+        X.i[a][b] = -Y.i[b][a];
+      }
+  } else {
+    load_mat<N>(M + (size_t)idx * 2 * N * N, X);
+  }
+}
+
 // Product of the lane's (up to) E consecutive matrices, later on the left
 // (the identity for a lane past the end).  The first matrix is loaded as
 // the start value: multiplying it into the identity would give the same
 // entries.
-template <int N, int E>
+template <int N, int E, bool REV = false>
 __device__ __forceinline__ void lane_product(const double* __restrict__ M, int64_t n, int64_t base,
                                              Mat<N>& Q) {
-  if (base < n) load_mat<N>(M + (size_t)base * 2 * N * N, Q);
+  if (base < n) load_element<N, REV>(M, n, base, Q);
   else set_identity<N>(Q);
 #pragma unroll
   for (int e = 1; e < E; ++e) {
     const int64_t idx = base + e;
     if (idx < n) {
       Mat<N> X;
-      load_mat<N>(M + (size_t)idx * 2 * N * N, X);
+      load_element<N, REV>(M, n, idx, X);
       premultiply<N>(X, Q);
     }
   }
@@ -55,12 +76,12 @@ __device__ __forceinline__ void lane_product(const double* __restrict__ M, int64
 
 // The lane's (up to) E consecutive matrices kept in X, and their product as
 // lane_product forms it (the same operations in the same order).
-template <int N, int E>
+template <int N, int E, bool REV = false>
 __device__ __forceinline__ void lane_product_keep(const double* __restrict__ M, int64_t n,
                                                   int64_t base, Mat<N>& Q, Mat<N> (&X)[E]) {
 #pragma unroll
   for (int e = 0; e < E; ++e)
-    if (base + e < n) load_mat<N>(M + (size_t)(base + e) * 2 * N * N, X[e]);
+    if (base + e < n) load_element<N, REV>(M, n, base + e, X[e]);
   if (base < n) Q = X[0];
   else set_identity<N>(Q);
 #pragma unroll
@@ -95,10 +116,10 @@ __device__ __forceinline__ void wave_scan(int lane, int L, Mat<N>& P) {
 
 // Inclusive products over a tile: lane j < L ends with P_j = Q_j ... Q_0,
 // Q_j the product of its E elements.  Every lane must call this.
-template <int N, int E>
+template <int N, int E, bool REV = false>
 __device__ __forceinline__ void lane_scan(const double* __restrict__ M, int64_t n, int64_t base,
                                           int lane, int L, Mat<N>& P) {
-  lane_product<N, E>(M, n, base, P);
+  lane_product<N, E, REV>(M, n, base, P);
   wave_scan<N>(lane, L, P);
 }
 
@@ -106,13 +127,13 @@ __device__ __forceinline__ void lane_scan(const double* __restrict__ M, int64_t 
 // wave per tile: the inclusive product of the last lane holding elements,
 // so that a tile's aggregate is bit for bit the total that tile_apply's
 // scan forms.  M points at element 0 of the sequence, n its length.
-template <int N, int E>
+template <int N, int E, bool REV = false>
 __device__ __forceinline__ void tile_reduce(const double* __restrict__ M, int64_t n, int64_t tile,
                                             int lane, double* __restrict__ agg_out) {
   const int64_t base = tile * (64 * E) + (int64_t)lane * E;
   const int L = lanes_with_data<E>(n, tile);
   Mat<N> P;
-  lane_scan<N, E>(M, n, base, lane, L, P);
+  lane_scan<N, E, REV>(M, n, base, lane, L, P);
   if (lane == L - 1 && agg_out) store_mat<N>(agg_out, P);
 }
 
@@ -121,7 +142,7 @@ __device__ __forceinline__ void tile_reduce(const double* __restrict__ M, int64_
 // lane's first element is P_{lane-1} start (start for lane 0), carried
 // through its elements; writes before[idx] (and spin, after_last) for the
 // lane's elements base .. base + E - 1 below n.  Every lane must call this.
-template <int N, int E, bool KEEP>
+template <int N, int E, bool KEEP, bool REV = false>
 __device__ __forceinline__ void tile_walk(const Mat<N>& P, const Mat<N> (&kept)[KEEP ? E : 1],
                                           const double* __restrict__ M, int64_t n, int64_t base,
                                           int lane, bool valid, const double* sr,
@@ -146,7 +167,7 @@ __device__ __forceinline__ void tile_walk(const Mat<N>& P, const Mat<N> (&kept)[
       if (spin) project_spin<N>(vr, vi, spin + 3 * idx);
       Mat<N> Y;
       if constexpr (KEEP) Y = kept[e];
-      else load_mat<N>(M + (size_t)idx * 2 * N * N, Y);
+      else load_element<N, REV>(M, n, idx, Y);
       double wr_[N], wi_[N];
       matvec<N>(Y, vr, vi, wr_, wi_);
 #pragma unroll
@@ -171,7 +192,7 @@ __device__ __forceinline__ void tile_walk(const Mat<N>& P, const Mat<N> (&kept)[
 // <J_x>, <J_y>, <J_z> of every state written.  Every lane must call this.
 // KEEP: the lane's matrices stay in registers from the scan to the walk
 // (one read of M instead of two); the values and operations are the same.
-template <int N, int E, bool KEEP = false>
+template <int N, int E, bool KEEP = false, bool REV = false>
 __device__ __forceinline__ void tile_apply(const double* __restrict__ M, int64_t n, int64_t tile,
                                            int lane, bool valid, const double* __restrict__ start,
                                            double* __restrict__ before,
@@ -187,10 +208,10 @@ __device__ __forceinline__ void tile_apply(const double* __restrict__ M, int64_t
   }
   Mat<N> P;
   Mat<N> kept[KEEP ? E : 1];
-  if constexpr (KEEP) lane_product_keep<N, E>(M, n, base, P, kept);
-  else lane_product<N, E>(M, n, base, P);
+  if constexpr (KEEP) lane_product_keep<N, E, REV>(M, n, base, P, kept);
+  else lane_product<N, E, REV>(M, n, base, P);
   wave_scan<N>(lane, lanes_with_data<E>(n, tile), P);
-  tile_walk<N, E, KEEP>(P, kept, M, n, base, lane, valid, sr, si, before, after_last, spin);
+  tile_walk<N, E, KEEP, REV>(P, kept, M, n, base, lane, valid, sr, si, before, after_last, spin);
 }
 
 // The state entering element w of a sequence of n <= 64 E elements that

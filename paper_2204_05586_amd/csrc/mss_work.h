@@ -67,6 +67,9 @@ struct DevWork {
   int64_t n_items = 0;
   int n_levels = 0;
   int scan_e = kScanPerLane;
+  // the scan's sequences are the descriptors' operators reversed and
+  // conjugate-transposed (scan_e is then kScanPerLane)
+  bool reversed = false;
   // chained runs
   int64_t n_units = 0;
   int32_t n_groups = 0;

@@ -45,7 +45,7 @@ __device__ __forceinline__ int find_segment(const int64_t* __restrict__ prefix, 
   int lo = 0, hi = n - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (prefix[mid] <= x) lo = mid;
+    if (as_constant(prefix)[mid] <= x) lo = mid;
     else hi = mid - 1;
   }
   return lo;
@@ -106,7 +106,7 @@ __device__ __forceinline__ int64_t level_geometry(const SimDesc& s, int level, s
   return n;
 }
 
-template <int N, int E>
+template <int N, int E, bool REV>
 __device__ __forceinline__ void work_reduce_tile(const SimDesc& s, int level, int64_t local,
                                                  int lane) {
   size_t off = 0;
@@ -116,10 +116,11 @@ __device__ __forceinline__ void work_reduce_tile(const SimDesc& s, int level, in
   const int64_t n_up = level_geometry<N, E>(s, level + 1, &up_off);
   (void)n_up;
   double* out = s.scan_ws + up_off + (size_t)local * 2 * N * N;
-  tile_reduce<N, E>(M, n, local, lane, out);
+  if (REV && level == 0) tile_reduce<N, E, REV>(M, n, local, lane, out);
+  else tile_reduce<N, E>(M, n, local, lane, out);
 }
 
-template <int N, int E>
+template <int N, int E, bool REV>
 __device__ __forceinline__ void work_apply_tile(const SimDesc& s, int level, int64_t local,
                                                 int lane) {
   size_t off = 0;
@@ -134,32 +135,38 @@ __device__ __forceinline__ void work_apply_tile(const SimDesc& s, int level, int
     const int64_t n_up = level_geometry<N, E>(s, level + 1, &up_off);
     start = s.scan_ws + up_off + (size_t)n_up * 2 * N * N + (size_t)local * 2 * N;
   }
-  tile_apply<N, E, (E * 2 * N * N <= 36)>(M, n, local, lane, true, start, before,
-                                           level == 0 ? s.psi_final : nullptr);
+  constexpr bool kKeep = E * 2 * N * N <= 36;
+  double* last = level == 0 ? s.psi_final : nullptr;
+  if (REV && level == 0)
+    tile_apply<N, E, kKeep, REV>(M, n, local, lane, true, start, before, last);
+  else
+    tile_apply<N, E, kKeep>(M, n, local, lane, true, start, before, last);
 }
 
-template <int E>
+template <int E, bool REV>
 __global__ void __launch_bounds__(256) work_reduce_kernel(const ScanWorkArgs A) {
   const int lane = threadIdx.x & 63;
-  const int64_t tile = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t tile = (int64_t)blockIdx.x * (blockDim.x >> 6) +
+                       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (tile >= A.n_tiles) return;  // the whole wave leaves together
   const int i = find_segment(A.tiles, A.n_sims, tile);
-  const int64_t local = tile - A.tiles[i];
-  const SimDesc& s = A.sims[i];
-  if (s.spin_twice == 2) work_reduce_tile<3, E>(s, A.level, local, lane);
-  else work_reduce_tile<2, E>(s, A.level, local, lane);
+  const int64_t local = tile - as_constant(A.tiles)[i];
+  const SimDesc s = load_constant(A.sims + i);
+  if (s.spin_twice == 2) work_reduce_tile<3, E, REV>(s, A.level, local, lane);
+  else work_reduce_tile<2, E, REV>(s, A.level, local, lane);
 }
 
-template <int E>
+template <int E, bool REV>
 __global__ void __launch_bounds__(256) work_apply_kernel(const ScanWorkArgs A) {
   const int lane = threadIdx.x & 63;
-  const int64_t tile = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t tile = (int64_t)blockIdx.x * (blockDim.x >> 6) +
+                       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (tile >= A.n_tiles) return;  // the whole wave leaves together
   const int i = find_segment(A.tiles, A.n_sims, tile);
-  const int64_t local = tile - A.tiles[i];
-  const SimDesc& s = A.sims[i];
-  if (s.spin_twice == 2) work_apply_tile<3, E>(s, A.level, local, lane);
-  else work_apply_tile<2, E>(s, A.level, local, lane);
+  const int64_t local = tile - as_constant(A.tiles)[i];
+  const SimDesc s = load_constant(A.sims + i);
+  if (s.spin_twice == 2) work_apply_tile<3, E, REV>(s, A.level, local, lane);
+  else work_apply_tile<2, E, REV>(s, A.level, local, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -388,28 +395,29 @@ hipError_t launch_work_chained(const DevWork& w, void* ws, int grid_blocks, hipS
   return hipGetLastError();
 }
 
-template <int E>
+template <int E, bool REV>
 static void scan_levels(const DevWork& w, hipStream_t st) {
   for (int l = 0; l < w.n_levels; ++l) {
     const int64_t tiles = w.reduce_total[l];
     if (!tiles) continue;
     ScanWorkArgs a{w.sims, w.reduce_tiles[l], tiles, w.n_sims, l};
-    hipLaunchKernelGGL(work_reduce_kernel<E>, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st,
+    hipLaunchKernelGGL((work_reduce_kernel<E, REV>), dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st,
                        a);
   }
   for (int l = w.n_levels; l >= 0; --l) {
     const int64_t tiles = w.apply_total[l];
     if (!tiles) continue;
     ScanWorkArgs a{w.sims, w.apply_tiles[l], tiles, w.n_sims, l};
-    hipLaunchKernelGGL(work_apply_kernel<E>, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st,
+    hipLaunchKernelGGL((work_apply_kernel<E, REV>), dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st,
                        a);
   }
 }
 
 hipError_t launch_work_scan(const DevWork& w, hipStream_t st) {
-  if (w.scan_e == 2) scan_levels<2>(w, st);
-  else if (w.scan_e == 8) scan_levels<8>(w, st);
-  else scan_levels<4>(w, st);
+  if (w.reversed) scan_levels<kScanPerLane, true>(w, st);
+  else if (w.scan_e == 2) scan_levels<2, false>(w, st);
+  else if (w.scan_e == 8) scan_levels<8, false>(w, st);
+  else scan_levels<4, false>(w, st);
   return hipGetLastError();
 }
 

@@ -69,3 +69,33 @@ def test_gradients_match_the_oracle(dev, oracle, pair, tau):
         assert abs(float(bufs["loss"][i]) - loss) <= 1e-12, i
         assert np.max(np.abs(got - grad)) <= 1e-11 * max(np.max(np.abs(grad)), 1.0), i
     plan.close()
+
+
+# A few short simulations leave the device idle, so the backward pass gives an
+# interval as many lanes as it has fine steps for, up to 16: one step a lane,
+# uneven shares, and interval counts that do not fill a wave.  The mixed list
+# takes the lanes of its shortest.
+@pytest.mark.parametrize("fine", [(1,), (2,), (3,), (5,), (16,), (17,), (33, 70)])
+@pytest.mark.parametrize("samples", [1, 3, 16, 67])
+def test_interval_split_over_lanes(dev, oracle, fine, samples):
+    from paper_2204_05586_amd import native
+    probs = []
+    for spin in (1, 2):
+        for j, L in enumerate(fine):
+            rng = np.random.default_rng(100 * spin + 10 * samples + j)
+            dt = 0.01 * L
+            terms = _terms("segments", samples * dt) + [W.Term(W.CONST, W.Z, a=1.2)]
+            probs.append(W.Problem(spin, terms, 0.0, dt, samples, L, 28 if spin == 2 else 0,
+                                   bool((j + samples) % 2), params=rng.uniform(0.3, 1.0, 15),
+                                   psi0=W.random_state(spin + 1, rng)))
+    plan = native.AdjointPlan(probs, 1)
+    bufs = plan.allocate()
+    print(f"[gpu] adjoint lanes L={fine} K={samples}", flush=True)
+    plan.run(bufs)
+    dev.cuda.synchronize()
+    for i, p in enumerate(probs):
+        loss, grad = oracle.adjoint_population(p, 1)
+        assert abs(float(bufs["loss"][i]) - loss) <= 1e-12, i
+        got = plan.grad_of(bufs, i).cpu().numpy()
+        assert np.max(np.abs(got - grad)) <= 1e-11 * max(np.max(np.abs(grad)), 1.0), i
+    plan.close()
