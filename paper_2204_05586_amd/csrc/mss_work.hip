@@ -135,7 +135,12 @@ __device__ __forceinline__ void work_apply_tile(const SimDesc& s, int level, int
     const int64_t n_up = level_geometry<N, E>(s, level + 1, &up_off);
     start = s.scan_ws + up_off + (size_t)n_up * 2 * N * N + (size_t)local * 2 * N;
   }
-  constexpr bool kKeep = E * 2 * N * N <= 36;
+  // the lane's operators stay in registers from the scan to the walk where
+  // they fit, spin-1 at E = 4 included: that leaves one wave a SIMD, but the
+  // second read of the operators (which at these sizes misses L2) is what the
+  // pass waits for: scans of 9.3e5, 7.6e6 and 3.1e7 spin-1 operators 114, 839
+  // and 3,279 us with it, 105, 738 and 2,743 without
+  constexpr bool kKeep = E * 2 * N * N <= 72;
   double* last = level == 0 ? s.psi_final : nullptr;
   if (REV && level == 0)
     tile_apply<N, E, kKeep, REV>(M, n, local, lane, true, start, before, last);
