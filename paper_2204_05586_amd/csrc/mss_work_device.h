@@ -169,14 +169,17 @@ __device__ __forceinline__ bool chain_receive(ChainSlot* slot, unsigned tag, Cha
   const bool mine = lane < 4 * N;
   bool ok = true;
   const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-  for (;;) {
+  for (int poll = 0;; ++poll) {
     if (wave_uniform(__all(!mine || (unsigned)(v >> 32) == tag))) break;
-    // not there yet: give up at once if a wait of this run already ran out
-    unsigned long long f = 0ull;
-    if (lane == 0) f = chain_read(&sync->failed);
-    if (wave_uniform(f != 0ull)) {
-      ok = false;
-      break;
+    // not there yet: give up if a wait of this run already ran out (looked up
+    // at the wait's first poll and then now and then: one word for all waves)
+    if ((poll & 31) == 0) {
+      unsigned long long f = 0ull;
+      if (lane == 0) f = chain_read(&sync->failed);
+      if (wave_uniform(f != 0ull)) {
+        ok = false;
+        break;
+      }
     }
     if (__builtin_amdgcn_s_memrealtime() - t0 > wait_ticks) {
       ok = false;
@@ -185,7 +188,17 @@ __device__ __forceinline__ bool chain_receive(ChainSlot* slot, unsigned tag, Cha
                                     __HIP_MEMORY_SCOPE_AGENT);
       break;
     }
+    // The slot tells how many units are still to pass before this one's turn;
+    // each takes some 2 us, and the wave sleeps half a microsecond for each
+    // of up to 64.  With one short sleep for all, every wave in line polled
+    // the same words and the failure word, and with fewer simulations than
+    // waves those polls were what a hand-off waited for: 512 sensing
+    // simulations of 10 to 100 ms 54 ms, now 8.9; 16 of 50 to 100 ms 58 and
+    // 1.9 (4096 of 10 to 100 ms: 72.8 and 69.3).
+    const unsigned have = (unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32));
+    const unsigned ahead = tag - 1u - have;  // 0: the unit before is the next to write
     __builtin_amdgcn_s_sleep(2);
+    for (unsigned i = 0; i < min(ahead, 64u); ++i) __builtin_amdgcn_s_sleep(16);
     if (mine) v = chain_read(&slot->w[lane]);
   }
   const unsigned lo32 = (unsigned)v;
@@ -285,22 +298,28 @@ __device__ __forceinline__ void chained_unit(const IntegrateWorkArgs& A, const S
   // not unrolled), so that nothing but parked operators outlives an
   // integration
   Mat<N> U;
+  const int wslot = wave_slot();
 #pragma unroll 1
   for (int e = 0;; ++e) {
     const int64_t k = k0 + e;
     const bool active = k < s.K_total;
+    // once an interval: at every fine step it costs more than it evens out
+    // (4096 simulations of 2,000 to 20,000 intervals: 7.04 and 7.21 ms; 512
+    // of 10 to 100 ms: 9.1 without a turn of its own for each unit, 9.6 with,
+    // 10.3 never)
+    rotate_priority(e, wslot);
     double tk;
     bool done = false;
     if constexpr (N == 3 && has_full_basis<Terms>::value) {
       if (s.full) {
-        interval_operator<3, true, true>(source(A, s), s.params, s.t_start, s.dt_out, s.dt,
+        interval_operator<3, true>(source(A, s), s.params, s.t_start, s.dt_out, s.dt,
                                          s.n_fine, s.tau, s.frame, s.method, k, slice, sl,
                                          active, U, &tk);
         done = true;
       }
     }
     if (!done)
-      interval_operator<N, false, true>(source(A, s), s.params, s.t_start, s.dt_out, s.dt,
+      interval_operator<N>(source(A, s), s.params, s.t_start, s.dt_out, s.dt,
                                         s.n_fine, s.tau, s.frame, s.method, k, slice, sl,
                                         active, U, &tk);
     if (active && slice == 0 && s.U) store_mat<N>(s.U + (size_t)k * 2 * N * N, U);
