@@ -18,6 +18,13 @@ constexpr int kScanTile = 64 * kScanPerLane;
 // VGPRs (no spills); at sixteen the kernel spilled and the separate
 // launches of the general path were faster.
 constexpr int kTopWaves = 8;
+// Largest tile count that is scanned whole in one workgroup
+// (scan_small_kernel): one wave per SIMD of a CU.  With eight waves two share
+// a SIMD and its registers (spin-1 spills) and wave 0's run over the totals
+// grows: 10.4 us against 9.3 of the two launches at 2048 spin-1/2 operators,
+// 21.5 against 15.2 at 2048 spin-1 ones; at four tiles 7.1 against 9.0 and
+// 11.1 against 14.1.
+constexpr int kSmallWaves = 4;
 
 struct IntegrateArgs {
   FieldProgram fp;
@@ -79,6 +86,9 @@ hipError_t launch_scan_apply(int N, const double* M, int64_t n, const double* st
 hipError_t launch_scan_apply_fold(int N, const double* M, int64_t n, const double* A1, int64_t n1,
                                   const double* start, double* before, double* after_last,
                                   hipStream_t st, double* spin);
+// a whole scan of at most kSmallWaves tiles
+hipError_t launch_scan_small(int N, const double* M, int64_t n, const double* start,
+                             double* before, double* after_last, hipStream_t st, double* spin);
 hipError_t launch_scan_top(int N, const double* M1, int64_t n1, const double* start,
                            double* before1, hipStream_t st);
 
