@@ -111,24 +111,6 @@ size_t request_bytes(const mss_problem& p) {
   return b;
 }
 
-// A finished request's results into the caller's buffers (any of the three
-// may be absent), 16 bytes a lane and grid stride, in one launch: a copy by
-// the runtime is a launch for each array, some 10 us for states of 1 MB.
-// Counts in complex values.
-struct CopyOutArgs {
-  const double2* src[3];
-  double2* dst[3];
-  int64_t n[3];
-};
-
-__global__ void __launch_bounds__(256) copy_out_kernel(const CopyOutArgs A) {
-  const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t step = (int64_t)gridDim.x * blockDim.x;
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-    for (int64_t i = at; i < A.n[a]; i += step) A.dst[a][i] = A.src[a][i];
-}
-
 struct Inflight {
   int slot;
   std::vector<uint64_t> finishing;
@@ -527,36 +509,26 @@ mss_status mss_server_wait(mss_server* S, uint64_t ticket, double timeout_s,
 mss_status mss_server_copy_out(mss_server* S, uint64_t ticket, double* psi, double* psi_final,
                                double* U, void* stream) {
   if (!S) return api_fail(MSS_E_INVALID, "server is NULL");
-  CopyOutArgs c{};
+  const double *sp, *sf, *su;
+  size_t np, nf, nu;
   {
     std::lock_guard<std::mutex> lock(S->mu);
     auto it = S->reqs.find(ticket);
     if (it == S->reqs.end()) return api_fail(MSS_E_INVALID, "unknown ticket %llu", (unsigned long long)ticket);
     const Request& r = *it->second;
     if (r.state != MSS_REQ_DONE) return api_fail(MSS_E_NOTREADY, "request not done");
-    const double* src[3] = {r.d_psi, r.d_fin, r.d_U};
-    double* dst[3] = {psi, psi_final, U};
-    const int64_t n[3] = {r.prob.n_samples * r.N, r.N, r.prob.n_samples * r.N * r.N};
-    for (int a = 0; a < 3; ++a) {
-      c.src[a] = (const double2*)src[a];
-      c.dst[a] = (double2*)dst[a];
-      c.n[a] = dst[a] ? n[a] : 0;
-    }
+    sp = r.d_psi;
+    sf = r.d_fin;
+    su = r.d_U;
+    np = (size_t)r.prob.n_samples * r.N * 16;
+    nf = (size_t)r.N * 16;
+    nu = (size_t)r.prob.n_samples * r.N * r.N * 16;
   }
   hipStream_t st = (hipStream_t)stream;
-  const int64_t most = std::max(c.n[0], std::max(c.n[1], c.n[2]));
   hipError_t e = hipSuccess;
-  if (((uintptr_t)psi | (uintptr_t)psi_final | (uintptr_t)U) % 16 != 0) {
-    // a caller's 8-byte aligned buffer: the runtime's copies
-    for (int a = 0; a < 3 && e == hipSuccess; ++a)
-      if (c.n[a])
-        e = hipMemcpyAsync(c.dst[a], c.src[a], (size_t)c.n[a] * 16, hipMemcpyDeviceToDevice, st);
-  } else if (most > 0) {
-    // four values a lane keep enough loads in flight; at most 8 workgroups a CU
-    const int64_t blocks = std::min<int64_t>((most + 1023) / 1024, (int64_t)S->grid_cap * 4);
-    hipLaunchKernelGGL(copy_out_kernel, dim3((unsigned)blocks), dim3(256), 0, st, c);
-    e = hipGetLastError();
-  }
+  if (psi) e = hipMemcpyAsync(psi, sp, np, hipMemcpyDeviceToDevice, st);
+  if (e == hipSuccess && psi_final) e = hipMemcpyAsync(psi_final, sf, nf, hipMemcpyDeviceToDevice, st);
+  if (e == hipSuccess && U) e = hipMemcpyAsync(U, su, nu, hipMemcpyDeviceToDevice, st);
   if (e != hipSuccess) return api_hip_fail(e, "copy out");
   return api_ok();
 }
