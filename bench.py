@@ -43,14 +43,14 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6  # 256 CU x 2.4 GHz x 128 FP64 flop/clk
 # the sources are unchanged.
 MEASURED_TRAFFIC = {
     ("mss_user_work_chained", "batched_sensing"): {
-        "src": "3cddbfb6a0a9c8eb",
-        "fetch_kib": 284383.0, "write_kib": 24306971.7,
-        "bytes": int(round((284383.0 * 2.000 + 24306971.7 * 1.000) * 1024)),
+        "src": "39b71392e1a59c25",
+        "fetch_kib": 504807.8, "write_kib": 22139089.6,
+        "bytes": int(round((504807.8 * 2.000 + 22139089.6 * 1.000) * 1024)),
     },
     ("mss_user_work_integrate", "batched_sensing"): {
-        "src": "3cddbfb6a0a9c8eb",
-        "fetch_kib": 3700.7, "write_kib": 64036245.0,
-        "bytes": int(round((3700.7 * 2.000 + 64036245.0 * 1.000) * 1024)),
+        "src": "39b71392e1a59c25",
+        "fetch_kib": 6540.4, "write_kib": 63962252.5,
+        "bytes": int(round((6540.4 * 2.000 + 63962252.5 * 1.000) * 1024)),
     },
 }
 
@@ -81,13 +81,39 @@ PAPER_CONTEXT = {"workload": "one 100 ms spin-1 sensing simulation, 1e6 CF4 step
 
 
 def spin_one_flops_per_fine_step(tau: int) -> int:
-    """Algorithmic FP64 flops of one spin-1 CF4 fine step as computed: two
-    Lie-Trotter exponentials of tau residual squarings of a complex symmetric
-    3x3 matrix (six entries: 96 flops each, counting a fused multiply-add as
-    two) plus two general 3x3 complex products into the interval operator
-    (27 complex multiply-adds = 216 flops each).  Angle set-up and the
-    phases put back once per exponential are not counted."""
+    """Algorithmic FP64 flops of one spin-1 CF4 fine step by residual
+    squarings (large angles or small tau only): two Lie-Trotter exponentials
+    of tau squarings of a complex symmetric 3x3 matrix (six entries: 96 flops
+    each, counting a fused multiply-add as two) plus two general 3x3 complex
+    products into the interval operator (27 complex multiply-adds = 216 flops
+    each).  Angle set-up and the phases put back once per exponential are not
+    counted."""
     return 2 * tau * 96 + 2 * 216
+
+
+# Algorithmic FP64 flops of one spin-1 exponential in closed form, as the
+# integrator computes it for angles up to 2^-6: the generator's entries and
+# invariants (20), the two real Horner recursions to G^6 and G^7 (22) and the
+# nine complex entries (71).
+SERIES_EXPONENTIAL_FLOPS = 20 + 22 + 71
+# The same in the full su(3) basis: entries and invariants (56), the
+# recursions (22), the squared generator (52) and the nine entries (63).
+SERIES_FULL_EXPONENTIAL_FLOPS = 56 + 22 + 52 + 63
+# One product into two columns of the interval operator (18 complex
+# multiply-adds of 8 flops; the third column is formed once per interval),
+# and into all three (full su(3) basis).
+PRODUCT_FLOPS = 18 * 8
+FULL_PRODUCT_FLOPS = 27 * 8
+
+
+def spin_one_executed_flops_per_fine_step(tau: int, exponentials: int = 2) -> int:
+    """Algorithmic FP64 flops of one spin-1 fine step as executed on the
+    sensing workloads, whose angles (below 2^-6) take the closed form from
+    tau = 20 on; `exponentials` is 2 for CF4 and 1 for the Euler methods.
+    Field samples, frame rotations and angle set-up are not counted."""
+    if tau < 20:
+        return exponentials * (tau * 96 + 216)
+    return exponentials * (SERIES_EXPONENTIAL_FLOPS + PRODUCT_FLOPS)
 
 
 # Algorithmic FP64 flops of one state update psi_{k+1} = U_k psi_k (spin-1:
@@ -538,20 +564,16 @@ def bench_next_rows(reps: int = 20) -> dict:
     for name, method in (("midpoint", W.MIDPOINT), ("heun", W.HEUN)):
         bare = prob.replace(terms=[], method=method)
         ms = timed(lambda: smp.integrate(bare, params, U, stream=stream))
-        # one exponential of tau symmetric squarings and one product per fine step
-        out[f"f2_{name}"] = alu(96 * tau + 216, ms)
+        out[f"f2_{name}"] = alu(spin_one_executed_flops_per_fine_step(tau, 1), ms)
     smp.close()
     user = native.Sampler(SENSING_USER_SOURCE)
     bare = prob.replace(terms=[])
     ms = timed(lambda: user.integrate(bare, params, U, stream=stream))
-    out["f3_user_sampler"] = alu(spin_one_flops_per_fine_step(tau), ms)
+    out["f3_user_sampler"] = alu(spin_one_executed_flops_per_fine_step(tau), ms)
     user.close()
     full = prob.replace(terms=list(prob.terms) + [W.Term(W.COS, W.V1, a=300.0, f=700e3)])
     ms = timed(lambda: native.integrate(full, params, U, stream=stream))
-    # per exponential: the Taylor residual (3 products) and tau general
-    # squarings (27 complex multiply-adds = 216 flops each); two per step,
-    # plus the two products into U
-    out["f4_full_su3"] = alu(2 * (3 * 216 + tau * 216) + 2 * 216, ms)
+    out["f4_full_su3"] = alu(2 * (SERIES_FULL_EXPONENTIAL_FLOPS + FULL_PRODUCT_FLOPS), ms)
     psi = torch.empty((K, N), dtype=torch.complex128, device="cuda")
     fin = torch.empty((N,), dtype=torch.complex128, device="cuda")
     ws = native.alloc_workspace(native.propagate_workspace_size(prob.spin_twice, K))
@@ -748,7 +770,7 @@ def main():
 
     roofline = None
     if args.workload != "spin_half_rabi":
-        flops = spin_one_flops_per_fine_step(tau) * fine
+        flops = spin_one_executed_flops_per_fine_step(tau) * fine
         if args.workload == "batched_sensing":
             flops += STATE_UPDATE_FLOPS * intervals  # the states, formed in the same launch
         achieved = flops / (integ_ms * 1e-3) / 1e12

@@ -11,8 +11,9 @@
  * cf4_implementation) inside a per-interval rotating frame (Sec.
  * "Dynamically rotating frame", eq. exit_rotating_frame), with an analytic
  * SU(2) exponential for spin-1/2 and the Lie-Trotter exponentiator with
- * 2^tau residual squarings for spin-1 (Sec. "Lie-Trotter based
- * exponentiator", eq. lie_trotter_4).  The state series is the ordered
+ * tau residual squarings for spin-1 (Sec. "Lie-Trotter based
+ * exponentiator", eq. lie_trotter_4), in closed form wherever the two agree
+ * to rounding.  The state series is the ordered
  * product psi_0 = psi_init, psi_{k+1} = U_k psi_k (Sec. "Discretization and
  * parallelization", eq. integration_compilation), computed on the GPU as
  * an associative prefix product.
@@ -96,7 +97,8 @@ typedef enum mss_term_kind {
  * problem with a term on U_1, U_2, V_1 or V_2 runs the full-basis
  * exponentiator: exp(-i G) by scaling and squaring, the residual of
  * exp(-i G / 2^tau) from its degree-4 Taylor polynomial, then the tau
- * residual squarings (n_squares); in the rotating frame (u1 + i u2) turns
+ * residual squarings (n_squares), in closed form wherever the two agree to
+ * rounding; in the rotating frame (u1 + i u2) turns
  * with e^{-2i w_r t} and (v1 + i v2) with e^{-i w_r t}.  Such problems
  * have no adjoint and no specialised sampler (MSS_E_UNSUPPORTED). */
 typedef enum mss_component {
@@ -242,7 +244,7 @@ mss_status mss_solve(const mss_problem* p, const double* params, const double* p
  * time t (s); f_q is ignored for spin-1/2.  params is the device parameter
  * vector passed to mss_sampler_integrate (NULL when n_params == 0).  The
  * source is compiled after the library's device header, so namespace mss
- * (e.g. mss::sincos_cw, accurate for phases up to 1.5e6 rad) and the device
+ * (e.g. mss::sincos_cw, accurate for phases below 2^30 rad) and the device
  * math library are available; flags: gfx950, -O3, C++17, fused multiply-add
  * contraction as hipcc's default (put `#pragma clang fp contract(off)` in
  * the function to fix its evaluation order).  The code must be safe to run
