@@ -376,13 +376,12 @@ def spin_projection(psi, stream=None):
     return out
 
 
-def _upload(prob, device, stream):
+def _upload(prob, device):
     """(params or None, psi0) on the device, one pinned and asynchronous copy
-    on the stream of the solve (a copy for each from pageable memory waits for
+    on the current stream (a copy for each from pageable memory waits for
     the GPU twice: with it and the problem packed four times, evaluate() took
     76 us for 2,000 spin-1 intervals and takes 42; 3e5 spin-1/2 intervals 148
     and 108)."""
-    import contextlib
     import torch
     psi0 = np.asarray(prob.psi0, dtype=np.complex128).ravel()
     params = np.asarray(prob.params, dtype=np.float64).ravel()
@@ -391,9 +390,28 @@ def _upload(prob, device, stream):
     flat = host.numpy()
     flat[:n] = psi0.view(np.float64)
     flat[n:] = params
-    with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
-        dev = host.to(device, non_blocking=True)
+    dev = host.to(device, non_blocking=True)
     return (dev[n:] if params.size else None), dev[:n]
+
+
+def _lend(stream, *tensors) -> None:
+    """Tensors of the current stream's memory pool (or None) to the work about
+    to be launched on `stream`: it starts after everything queued on the
+    current stream, which may still use a block that one of them has taken
+    over, and no block goes to a later tensor before that work is done."""
+    import torch
+    if stream is None:
+        return
+    device = next(t.device for t in tensors if t is not None)
+    current = torch.cuda.current_stream(device)
+    if int(stream.cuda_stream) == int(current.cuda_stream):
+        return
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(int(stream.cuda_stream), device=device)
+    stream.wait_stream(current)
+    for t in tensors:
+        if t is not None:
+            t.record_stream(stream)
 
 
 def solve(prob, store_u: bool = False, want_time: bool = False, device="cuda",
@@ -401,7 +419,10 @@ def solve(prob, store_u: bool = False, want_time: bool = False, device="cuda",
     """Allocate outputs on the device and run the whole path (mss_solve, or
     mss_sampler_solve when a sampler supplies the field; with want_spin the
     integrator then mss_propagate_spin).  Returns torch tensors: psi [K, N],
-    psi_final [N], U [K, N, N] or None, time [K] or None, spin [K, 3] or None."""
+    psi_final [N], U [K, N, N] or None, time [K] or None, spin [K, 3] or None,
+    allocated on the current stream.  With a stream of its own the work runs
+    after what is queued on the current stream, and the caller orders what
+    reads the results after it."""
     return _solve(prob, PackedProblem(prob), store_u, want_time, device, stream, sampler,
                   want_spin)
 
@@ -412,7 +433,7 @@ def _solve(prob, pk: PackedProblem, store_u, want_time, device, stream, sampler,
     import torch
     L = lib()
     K, N = int(prob.n_samples), int(prob.spin_twice) + 1
-    params, psi0 = _upload(prob, device, stream)
+    params, psi0 = _upload(prob, device)
     psi = torch.empty((K, N), dtype=torch.complex128, device=device)
     fin = torch.empty((N,), dtype=torch.complex128, device=device)
     U = torch.empty((K, N, N), dtype=torch.complex128, device=device) if store_u else None
@@ -420,18 +441,20 @@ def _solve(prob, pk: PackedProblem, store_u, want_time, device, stream, sampler,
     st = _stream(stream)
     if want_spin:
         Uw = U if U is not None else torch.empty((K, N, N), dtype=torch.complex128, device=device)
+        spin = torch.empty((K, 3), dtype=torch.float64, device=device)
+        ws = alloc_workspace(propagate_workspace_size(prob.spin_twice, K), device)
+        _lend(stream, psi0, params, psi, fin, Uw, time, spin, ws)
         if sampler is None:
             check(L.mss_integrate(pk.ref, _ptr(params), _ptr(Uw), _ptr(time), None, st))
         else:
             check(L.mss_sampler_integrate(sampler._h, pk.ref, _ptr(params), _ptr(Uw), _ptr(time),
                                           None, st))
-        spin = torch.empty((K, 3), dtype=torch.float64, device=device)
-        ws = alloc_workspace(propagate_workspace_size(prob.spin_twice, K), device)
         propagate(prob.spin_twice, Uw, psi0, psi, fin, ws, stream, spin=spin)
         return {"psi": psi, "psi_final": fin, "U": U, "time": time, "spin": spin}
     n = C.c_size_t()
     check(L.mss_workspace_size(pk.ref, int(bool(store_u)), C.byref(n)))
     ws = alloc_workspace(n.value, device)
+    _lend(stream, psi0, params, psi, fin, U, time, ws)
     args = (pk.ref, _ptr(params), _ptr(psi0), _ptr(U), _ptr(psi), _ptr(fin), _ptr(time), _ptr(ws),
             int(ws.numel()), st)
     if sampler is None:
