@@ -431,6 +431,11 @@ def _solve(prob, pk: PackedProblem, store_u, want_time, device, stream, sampler,
            want_spin) -> dict:
     """solve() for a problem that is packed already."""
     import torch
+    if torch.cuda.is_current_stream_capturing():
+        # the upload would be recorded with the address of a host block that
+        # goes to another call once this one is over
+        raise RuntimeError("solve() cannot be captured: it uploads its inputs from the host; "
+                           "capture solve_into() on buffers that are kept")
     L = lib()
     K, N = int(prob.n_samples), int(prob.spin_twice) + 1
     params, psi0 = _upload(prob, device)
