@@ -156,6 +156,13 @@ __device__ __forceinline__ bool wave_uniform(bool b) {
   return __builtin_amdgcn_readfirstlane((int)b) != 0;
 }
 
+// Units still to write a slot before the one with tag `tag`, when one of its
+// words carries the tag `have`.  None where that word is the waited-for unit's
+// already: the others are then about to arrive.
+__device__ constexpr unsigned units_ahead(unsigned tag, unsigned have) {
+  return have < tag ? tag - 1u - have : 0u;
+}
+
 // The state the unit with tag `tag` left in the slot (every lane receives
 // it): lanes 0 .. 4N - 1 hold one word each, v (read earlier), and read it
 // again until all carry the tag.  The loop's exits are wave-uniform.
@@ -196,7 +203,7 @@ __device__ __forceinline__ bool chain_receive(ChainSlot* slot, unsigned tag, Cha
     // simulations of 10 to 100 ms 54 ms, now 8.9; 16 of 50 to 100 ms 58 and
     // 1.9 (4096 of 10 to 100 ms: 72.8 and 69.3).
     const unsigned have = (unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32));
-    const unsigned ahead = tag - 1u - have;  // 0: the unit before is the next to write
+    const unsigned ahead = units_ahead(tag, have);
     __builtin_amdgcn_s_sleep(2);
     for (unsigned i = 0; i < min(ahead, 64u); ++i) __builtin_amdgcn_s_sleep(16);
     if (mine) v = chain_read(&slot->w[lane]);
