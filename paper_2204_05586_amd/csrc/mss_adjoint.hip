@@ -958,6 +958,7 @@ mss_status bind(mss_adjoint_plan* P, const double* params, const double* psi0, d
   if (e != hipSuccess) return api_hip_fail(e, "adjoint descriptor upload");
   const char* d = (const char*)P->desc;
   P->dfwd = device_view(P->fwd, d + P->f_base, P->f_sims, P->f_terms, P->f_red, P->f_app);
+  P->dfwd.lines = queue_lines(P->fwd, P->grid_blocks);
   P->dbwd = device_view(P->bwd, d + P->b_base, P->b_sims, P->b_terms, P->b_red, P->b_app);
   P->dbwd.reversed = true;
   for (int i = 0; i < 5; ++i) P->bound[i] = key[i];

@@ -259,6 +259,7 @@ mss_status create_plan(int32_t n, const mss_problem* problems, const int64_t* pa
   const int64_t blocks = (int64_t)cu * wps;  // 256-thread blocks: one wave per SIMD each
   const int64_t units = P->work.chained ? P->work.n_units : P->work.n_items;
   P->grid_blocks = (int)std::max<int64_t>(1, std::min(blocks, (units + 3) / 4));
+  P->dev.lines = queue_lines(P->work, P->grid_blocks);
   *out = P;
   return api_ok();
 }

@@ -302,6 +302,7 @@ void mss_server::run() {
       if (e == hipSuccess) {
         DevWork dw = device_view(ws, (const char*)desc[slot] + 256, o_sims, o_terms, o_red, o_app);
         const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(grid_cap, (ws.n_items + 3) / 4));
+        dw.lines = queue_lines(ws, blocks);
         e = launch_work_integrate(dw, (unsigned long long*)desc[slot], blocks, stream, nullptr,
                                   true);
         if (e == hipSuccess) e = launch_work_scan(dw, stream);

@@ -65,6 +65,7 @@ struct DevWork {
   std::vector<int64_t> reduce_total, apply_total;
   int32_t n_sims = 0;
   int64_t n_items = 0;
+  QueueLines lines = {0, 0, 0};
   int n_levels = 0;
   int scan_e = kScanPerLane;
   // the scan's sequences are the descriptors' operators reversed and
@@ -83,6 +84,10 @@ DevWork device_view(const WorkSet& w, const char* dev_base, size_t o_sims, size_
                     const std::vector<size_t>& o_reduce, const std::vector<size_t>& o_apply,
                     size_t o_chain = 0);
 
+// Where the waves of a launch of grid_blocks workgroups over the set's ranges
+// may take more than one item at a time (DevWork::lines; one at a time
+// without).
+QueueLines queue_lines(const WorkSet& w, int grid_blocks);
 // Enqueue the integrator (counter cleared by a kernel first, unless the
 // caller's stream has already zeroed it: counter_zeroed) over every range of
 // the work set; grid_blocks 256-thread workgroups.  user_fn: the work

@@ -44,6 +44,12 @@ struct ChainSlot {
 };
 static_assert(sizeof(ChainSlot) == 128, "one chain slot is 128 bytes");
 
+// Items of the queue at which a wave takes four at a time, [first, four), and
+// two, [four, two); one at a time elsewhere (queue_lines).
+struct QueueLines {
+  int64_t first, four, two;
+};
+
 // Head of a chained run's workspace: the unit counter and the tag of a
 // wait that ran out in this run (0 if none did), both cleared by the reset
 // kernel.
@@ -60,6 +66,7 @@ struct IntegrateWorkArgs {
   unsigned long long* counter;
   int64_t n_items;
   int32_t n_sims;
+  QueueLines lines;
   // chained runs only (n_items then counts units of kChainPerLane 64 / S
   // intervals): the interleaved unit order, the chain slots and the bound
   // of one wait (ticks of the 100 MHz real-time counter).  Units go round by round
@@ -486,19 +493,17 @@ constexpr int64_t kResidentWaves = 2048;
 // Increments of the one counter take effect 12 ns apart, whichever wave they
 // come from, so an increment an item bounds a launch: 7.1e6 items of
 // 64 spin-1 intervals of 10 fine steps took 85.1 ms, 12 ns each, where the
-// arithmetic takes 67.  So a wave takes four items at a time while more than
-// eight for every wave are left and two while more than four are, which
-// leaves enough single ones to even out the waves' rates (lines at half
-// that: 200 mixed simulations 584 us against 541; at twice that: a burst
-// of 24 requests 907 us against 820), and the waves resident from the start
-// begin with the item of their own number instead of 2,048 increments in a
-// row.  85.1 -> 67.1 ms; 200 mixed simulations with the scan 564 -> 541 us,
-// a burst of 24 served requests 1045 -> 820 us, the gradients of 256
-// instances 1946 -> 1843 us.
+// arithmetic takes 67.  So a wave takes four or two items at a time where
+// enough of them and enough work are left (queue_lines), and the waves
+// resident from the start begin with the item of their own number instead of
+// 2,048 increments in a row.  85.1 -> 67.1 ms; 200 mixed simulations with the
+// scan 574 -> 540 us, a burst of 24 served requests 1067 -> 840, the gradients
+// of 256 instances 1943 -> 1844.
 // While a whole grid's worth of items remains, the next ones are taken
 // before the current ones are worked on, so the counter's round trip
 // overlaps that work; near the end they are taken afterwards, so that the
 // last items go to idle waves.
+// A is the kernel's only argument.
 template <class Source>
 __device__ __forceinline__ void work_integrate_loop(const IntegrateWorkArgs& A,
                                                     const Source& source) {
@@ -513,7 +518,14 @@ __device__ __forceinline__ void work_integrate_loop(const IntegrateWorkArgs& A,
   int64_t end = item + 1;
   while (item < A.n_items) {
     const int64_t left = A.n_items - item;
-    const int take = left > 8 * waves ? 4 : left > 4 * waves ? 2 : 1;
+    // read from the kernel's arguments at every turn: held in registers through
+    // the items, the field programs' kernel spills more (200 mixed simulations
+    // 548 us against 542)
+    Constant<QueueLines>* lines =
+        (Constant<QueueLines>*)((uint64_t)__builtin_amdgcn_kernarg_segment_ptr() +
+                                __builtin_offsetof(IntegrateWorkArgs, lines));
+    asm volatile("" : "+s"(lines));
+    const int take = item < lines->first || item >= lines->two ? 1 : item < lines->four ? 4 : 2;
     const bool ahead = left > waves;
     int64_t next = 0;
     if (ahead && lane == 0) next = (int64_t)atomicAdd(A.counter, (unsigned long long)take);
