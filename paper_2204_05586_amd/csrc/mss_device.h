@@ -459,12 +459,16 @@ __device__ __forceinline__ void sincos_cw(double x, double* s, double* c) {
 
 // Tiny angles inside the exponentiators: below 2^-10 the Taylor series to
 // x^5 (sin) and x^6 (cos) is exact to far below one ulp (next terms
-// < 2e-22 relative); above it, sincos_cw.
+// < 2e-22 relative); above it, sincos_cw, with LEAF without a call for far
+// arguments.
+template <bool LEAF = false>
 __device__ __forceinline__ void sincos_small(double x, double* s, double* c) {
   if (fabs(x) < 0x1p-10) {
     const double x2 = x * x;
     *s = fma(x * x2, fma(x2, 1.0 / 120.0, -1.0 / 6.0), x);
     *c = fma(x2, fma(x2, fma(x2, -1.0 / 720.0, 1.0 / 24.0), -0.5), 1.0);
+  } else if (LEAF && !sincos_in_range(x)) {
+    sincos(x, s, c);
   } else {
     sincos_cw(x, s, c);
   }
@@ -545,6 +549,7 @@ struct Sym3 {
 // paper at phi = 0, the T_13 and T_22 misprints corrected); diagonals as
 // (e^{i b} - 1) - k S^2 e^{i b} with e^{i b} - 1 = -2 sin^2(b/2) + i sin b,
 // so nothing cancels.  Returns e^{i phi} = (theta_x + i theta_y) / rho.
+template <bool LEAF = false>
 __device__ __forceinline__ void lie_trotter_residual(const double th[4], int tau, Sym3& a,
                                                      double* ep_r, double* ep_i) {
   const double ninv = ldexp(1.0, -tau);
@@ -561,12 +566,12 @@ __device__ __forceinline__ void lie_trotter_residual(const double th[4], int tau
   *ep_r = epr;
   *ep_i = epi;
   double S, C;
-  sincos_small(0.5 * Phi, &S, &C);
+  sincos_small<LEAF>(0.5 * Phi, &S, &C);
   const double S2 = S * S;
   const double rs = kRsqrt2 * (2.0 * S * C);  // sin(Phi) / sqrt 2
   double sz, cz, sq, cq;
-  sincos_small(0.5 * z, &sz, &cz);           // e^{i z/2}
-  sincos_small(q * (1.0 / 6.0), &sq, &cq);   // e^{i q/6}
+  sincos_small<LEAF>(0.5 * z, &sz, &cz);           // e^{i z/2}
+  sincos_small<LEAF>(q * (1.0 / 6.0), &sq, &cq);   // e^{i q/6}
   // g = e^{iq/6} e^{-iz/2}, h = e^{iq/6} e^{iz/2}
   const double gr = fma(cq, cz, sq * sz), gi = fma(sq, cz, -cq * sz);
   const double hr = fma(cq, cz, -sq * sz), hi = fma(sq, cz, cq * sz);
@@ -674,28 +679,42 @@ __device__ __forceinline__ void sym_to_full(const Sym3& s, double d, double epr,
 // tau residual squarings a' <- (a' + 2I) a' (two per trip, alternating
 // between two register sets, so nothing is copied): E = P (I + a') P^H.  Any
 // tau and any angles; exp_one takes it only where the split at n = 2^tau can
-// be told from the exponential itself.  A call, so that the code is there
-// once and its registers bind no caller; arguments and result (28 registers)
-// pass in registers.
-struct SplitPower {
-  Sym3 a;
-  double epr, epi;  // e^{i phi}
-};
-__device__ __attribute__((noinline)) SplitPower split_power(double x, double y, double z, double q,
-                                                            int tau) {
-  const double th[4] = {x, y, z, q};
-  SplitPower p;
-  Sym3 b;
-  lie_trotter_residual(th, tau, p.a, &p.epr, &p.epi);
+// be told from the exponential itself.  Entries j of a' at 2j and 2j + 1, then
+// e^{i phi}.
+using SplitPower = double __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ SplitPower split_power(const double th[4], int tau) {
+  Sym3 a, b;
+  double epr, epi;
+  lie_trotter_residual<true>(th, tau, a, &epr, &epi);
   for (int s = 0; s + 2 <= tau; s += 2) {
-    residual_square(p.a, b);
-    residual_square(b, p.a);
+    residual_square(a, b);
+    residual_square(b, a);
   }
   if (tau & 1) {
-    residual_square(p.a, b);
-    p.a = b;
+    residual_square(a, b);
+    a = b;
   }
-  return p;
+  SplitPower v;
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    v[2 * j] = a.r[j];
+    v[2 * j + 1] = a.i[j];
+  }
+  v[12] = epr;
+  v[13] = epi;
+  return v;
+}
+// As a call, so that the code is there once and its registers bind no caller.
+// Arguments and result pass in registers (a structure of 14 doubles would come
+// back through memory), and nothing is called from it, so that its return
+// address stays in registers too: 1e5 spin-1 intervals of 10 fine steps at
+// tau = 0, 12 and 22, all angles by the squarings: 65, 115 and 148 us with a
+// structure and a call inside, 35, 93 and 133 now; without a call (integrators
+// that knew nothing but squarings) 32, 83 and 128.
+__device__ __attribute__((noinline)) SplitPower split_power_call(double x, double y, double z,
+                                                                 double q, int tau) {
+  const double th[4] = {x, y, z, q};
+  return split_power(th, tau);
 }
 
 // The spin-1 exponential in closed form.
@@ -843,6 +862,7 @@ constexpr double kLongSeries = 0.75;
 // 4096 spin-1 simulations, 4.5e7 intervals of 10 fine steps in one chained
 // launch: 54.2 ms with the squarings, 9.0 ms with the series; one of 2e5
 // intervals, scan included: 298 and 91 us.
+template <bool INLINE = false>
 __device__ __forceinline__ void exp_one(const double th[4], int tau, Mat<3>& E) {
   Gen3 g;
   generator(th, g);
@@ -853,8 +873,16 @@ __device__ __forceinline__ void exp_one(const double th[4], int tau, Mat<3>& E) 
   } else if (g.p <= fmin(most, kLongSeries)) {
     series<18, 17>(g.p, g.d, c, s);
   } else {  // also angles that are not finite
-    const SplitPower w = split_power(th[0], th[1], th[2], th[3], tau);
-    sym_to_full(w.a, 1.0, w.epr, w.epi, E);
+    SplitPower v;
+    if constexpr (INLINE) v = split_power(th, tau);
+    else v = split_power_call(th[0], th[1], th[2], th[3], tau);
+    Sym3 a;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      a.r[j] = v[2 * j];
+      a.i[j] = v[2 * j + 1];
+    }
+    sym_to_full(a, 1.0, v[12], v[13], E);
     return;
   }
   assemble(g, c, s, E);
@@ -862,13 +890,15 @@ __device__ __forceinline__ void exp_one(const double th[4], int tau, Mat<3>& E) 
 
 template <int N> struct Exponentiator;
 template <> struct Exponentiator<2> {
+  template <bool INLINE = false>
   static __device__ __forceinline__ void apply(const double th[4], int tau, Mat<2>& E) {
     exp_half(th, tau, E);
   }
 };
 template <> struct Exponentiator<3> {
+  template <bool INLINE = false>
   static __device__ __forceinline__ void apply(const double th[4], int tau, Mat<3>& E) {
-    exp_one(th, tau, E);
+    exp_one<INLINE>(th, tau, E);
   }
 };
 
@@ -1363,12 +1393,51 @@ __device__ __forceinline__ int wave_slot() {
   return (int)(__builtin_amdgcn_s_getreg(4 | (3 << 11)) & 15u);
 }
 
+// The fine steps l0 .. l1 of an interval, into R.  INLINE: with the
+// squarings in the loop instead of a call.
+template <int N, bool INLINE, class Terms>
+__device__ __forceinline__ void integrate_slice(const Terms& terms, const double* __restrict__ params,
+                                                const double (&fc)[4], double tk, int l0, int l1,
+                                                double dt, double wr, int tau, int method,
+                                                Running<N, false>& R) {
+  if (method == 0) {
+    NodeRotations rot;
+    if (wr != 0.0) rot.start(wr, l0, dt);
+    for (int l = l0; l < l1; ++l) {
+      double th1[4], th2[4];
+      cf4_angles(terms, params, fc, tk, l, dt, wr, rot, th1, th2);
+      if (wr != 0.0) rot.advance();
+      Mat<N> E;
+      Exponentiator<N>::template apply<INLINE>(th1, tau, E);
+      R.multiply(E);
+      Exponentiator<N>::template apply<INLINE>(th2, tau, E);
+      R.multiply(E);
+    }
+  } else {
+    for (int l = l0; l < l1; ++l) {
+      double th[4];
+      euler_angles(terms, params, fc, tk, l, dt, wr, method, th);
+      Mat<N> E;
+      Exponentiator<N>::template apply<INLINE>(th, tau, E);
+      R.multiply(E);
+    }
+  }
+}
+
+// Below this tau most angles take the squarings (2 pi 2 kHz over 50 ns, the
+// sensing drive's largest, from tau = 16 on none), and the integrator of a
+// compiled field has them in its loop: 31.5 us at tau = 0 and 88 at 12 against
+// 35 and 93 with the call.  Not the others: the interpreter gains 2 us of 44 and
+// 101, a chained run nothing, and every copy of a compiled field's loop is
+// compiled at run time.
+constexpr int kOftenSquared = 16;
+
 // Operator of one interval (rows a1-a9) computed by S = 2^sl cooperating
 // lanes: slice s integrates fine steps [s L / S, (s + 1) L / S) and the
 // partial products are combined in order with wave shuffles; the full
 // U_k (frame exit applied) ends up in the lane with s == 0.  Every lane of
 // the wave must call this (the shuffles need the whole wave).
-template <int N, bool FULL = false, class Terms>
+template <int N, bool FULL = false, bool OFTEN = false, class Terms>
 __device__ __forceinline__ void interval_operator(const Terms& terms, const double* __restrict__ params,
                                                   double t_start, double Dt, double dt, int L,
                                                   int tau, int frame, int method, int64_t k, int s,
@@ -1407,27 +1476,10 @@ __device__ __forceinline__ void interval_operator(const Terms& terms, const doub
           R.multiply(E);
         }
       }
-    } else if (method == 0) {
-      NodeRotations rot;
-      if (wr != 0.0) rot.start(wr, l0, dt);
-      for (int l = l0; l < l1; ++l) {
-        double th1[4], th2[4];
-        cf4_angles(terms, params, fc, tk, l, dt, wr, rot, th1, th2);
-        if (wr != 0.0) rot.advance();
-        Mat<N> E;
-        Exponentiator<N>::apply(th1, tau, E);
-        R.multiply(E);
-        Exponentiator<N>::apply(th2, tau, E);
-        R.multiply(E);
-      }
+    } else if (OFTEN && N == 3 && tau < kOftenSquared) {
+      integrate_slice<N, true>(terms, params, fc, tk, l0, l1, dt, wr, tau, method, R);
     } else {
-      for (int l = l0; l < l1; ++l) {
-        double th[4];
-        euler_angles(terms, params, fc, tk, l, dt, wr, method, th);
-        Mat<N> E;
-        Exponentiator<N>::apply(th, tau, E);
-        R.multiply(E);
-      }
+      integrate_slice<N, false>(terms, params, fc, tk, l0, l1, dt, wr, tau, method, R);
     }
   }
   R.whole(U);
@@ -1480,8 +1532,9 @@ __device__ __forceinline__ void integrate_lanes(const Terms& terms, const Interv
     }
   }
   if (!done)
-    interval_operator<N>(terms, g.params, g.t_start, g.dt_out, g.dt, g.L, g.tau, g.frame,
-                         g.method, k, s, sl, active, U, &tk);
+    interval_operator<N, false, !has_full_basis<Terms>::value>(
+        terms, g.params, g.t_start, g.dt_out, g.dt, g.L, g.tau, g.frame, g.method, k, s, sl, active,
+        U, &tk);
   if (active && s == 0) {
     store_mat<N>(g.U + (size_t)k * 2 * N * N, U);
     if (g.time) g.time[k] = tk;
