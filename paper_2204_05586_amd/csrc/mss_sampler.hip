@@ -3,6 +3,7 @@
 // mss_user_kernels.h, per-device loading of the code object, and the
 // integrator launches.  The device headers are embedded by the build
 // (mss_rtc_sources.inc) so the library needs no source tree at run time.
+#include <elf.h>
 #include <hip/hiprtc.h>
 #include <math.h>
 #include <stdio.h>
@@ -175,6 +176,82 @@ std::string specialised_source(const mss_term* terms, int n) {
   return s;
 }
 
+// One compilation of the program: its code object and log.
+mss_status compile(const std::string& program, std::vector<const char*>& names,
+                   std::vector<const char*>& texts, std::vector<const char*>& opts,
+                   std::vector<char>* code, std::string* log) {
+  hiprtcProgram prog = nullptr;
+  hiprtcResult r = hiprtcCreateProgram(&prog, program.c_str(), "user_field.hip", (int)names.size(),
+                                       texts.data(), names.data());
+  if (r != HIPRTC_SUCCESS)
+    return api_fail(MSS_E_DEVICE, "hiprtcCreateProgram: %s", hiprtcGetErrorString(r));
+  r = hiprtcCompileProgram(prog, (int)opts.size(), opts.data());
+  *log = program_log(prog);
+  if (r != HIPRTC_SUCCESS) {
+    (void)hiprtcDestroyProgram(&prog);
+    return api_fail_text(MSS_E_INVALID, std::string("user sampler failed to compile (") +
+                                            hiprtcGetErrorString(r) + "):\n" + *log);
+  }
+  size_t n = 0;
+  r = hiprtcGetCodeSize(prog, &n);
+  code->resize(n);
+  if (r == HIPRTC_SUCCESS && n > 0) r = hiprtcGetCode(prog, code->data());
+  (void)hiprtcDestroyProgram(&prog);
+  if (r != HIPRTC_SUCCESS || n == 0)
+    return api_fail(MSS_E_DEVICE, "hiprtcGetCode: %s", hiprtcGetErrorString(r));
+  return MSS_OK;
+}
+
+// Scratch bytes of a lane above which the plain and the work-queue integrator
+// get all 512 registers, one wave to a SIMD instead of two.  1e5 spin-1
+// intervals of 10 fine steps: a field of sixteen coefficients for each
+// component kept in registers has 304 bytes and takes 190 us (with 512
+// registers 214), one of sixteen harmonics 288 bytes and 123 us (143); sixteen
+// sines and cosines kept and multiplied have 1,440 bytes and take 563 us (298),
+// twenty-eight 2,976 bytes and 1569 (1294).
+constexpr uint32_t kScratchAtHalf = 512;
+
+// The most scratch memory of a lane among the integrators of a code object
+// (ELF), from their kernel descriptors; 0 if it cannot be told.
+uint32_t scratch_bytes(const std::vector<char>& code) {
+  Elf64_Ehdr eh;
+  if (code.size() < sizeof eh) return 0;
+  memcpy(&eh, code.data(), sizeof eh);
+  if (memcmp(eh.e_ident, ELFMAG, SELFMAG) != 0 || eh.e_shentsize != sizeof(Elf64_Shdr)) return 0;
+  const auto inside = [&](uint64_t off, uint64_t n) {
+    return off <= code.size() && n <= code.size() - off;
+  };
+  if (!inside(eh.e_shoff, (uint64_t)eh.e_shnum * sizeof(Elf64_Shdr))) return 0;
+  std::vector<Elf64_Shdr> sec(eh.e_shnum);
+  if (!sec.empty()) memcpy(sec.data(), code.data() + eh.e_shoff, sec.size() * sizeof(Elf64_Shdr));
+  uint32_t most = 0;
+  for (const Elf64_Shdr& t : sec) {
+    if (t.sh_type != SHT_DYNSYM || t.sh_link >= sec.size()) continue;
+    const Elf64_Shdr& names = sec[t.sh_link];
+    if (!inside(t.sh_offset, t.sh_size) || !inside(names.sh_offset, names.sh_size)) continue;
+    const std::string text(code.data() + names.sh_offset, names.sh_size);
+    for (uint64_t i = 0; i + sizeof(Elf64_Sym) <= t.sh_size; i += sizeof(Elf64_Sym)) {
+      Elf64_Sym y;
+      memcpy(&y, code.data() + t.sh_offset + i, sizeof y);
+      if (y.st_name >= text.size() || y.st_shndx >= sec.size()) continue;
+      const char* name = text.c_str() + y.st_name;
+      if (strcmp(name, "mss_user_integrate_2.kd") != 0 &&
+          strcmp(name, "mss_user_integrate_3.kd") != 0 &&
+          strcmp(name, "mss_user_work_integrate.kd") != 0)
+        continue;
+      // the descriptor: group segment bytes, then private segment bytes
+      const Elf64_Shdr& in = sec[y.st_shndx];
+      if (y.st_value < in.sh_addr) continue;
+      const uint64_t at = in.sh_offset + (y.st_value - in.sh_addr) + 4;
+      uint32_t bytes = 0;
+      if (!inside(at, sizeof bytes)) continue;
+      memcpy(&bytes, code.data() + at, sizeof bytes);
+      most = std::max(most, bytes);
+    }
+  }
+  return most;
+}
+
 }  // namespace
 
 namespace mss {
@@ -233,25 +310,14 @@ mss_status mss_sampler_create(const char* source, const char* const* options, in
   std::vector<const char*> opts(std::begin(kBaseOptions), std::end(kBaseOptions));
   for (int i = 0; i < n_options; ++i) opts.push_back(options[i]);
 
-  hiprtcProgram prog = nullptr;
-  hiprtcResult r = hiprtcCreateProgram(&prog, program.c_str(), "user_field.hip", (int)names.size(),
-                                       texts.data(), names.data());
-  if (r != HIPRTC_SUCCESS)
-    return api_fail(MSS_E_DEVICE, "hiprtcCreateProgram: %s", hiprtcGetErrorString(r));
-  r = hiprtcCompileProgram(prog, (int)opts.size(), opts.data());
-  std::string log = program_log(prog);
-  if (r != HIPRTC_SUCCESS) {
-    (void)hiprtcDestroyProgram(&prog);
-    return api_fail_text(MSS_E_INVALID, std::string("user sampler failed to compile (") +
-                                            hiprtcGetErrorString(r) + "):\n" + log);
+  std::vector<char> code;
+  std::string log;
+  mss_status st = compile(program, names, texts, opts, &code, &log);
+  if (st != MSS_OK) return st;
+  if (scratch_bytes(code) > kScratchAtHalf) {
+    opts.push_back("-DMSS_USER_ALL_REGISTERS");
+    if ((st = compile(program, names, texts, opts, &code, &log)) != MSS_OK) return st;
   }
-  size_t n = 0;
-  r = hiprtcGetCodeSize(prog, &n);
-  std::vector<char> code(n);
-  if (r == HIPRTC_SUCCESS && n > 0) r = hiprtcGetCode(prog, code.data());
-  (void)hiprtcDestroyProgram(&prog);
-  if (r != HIPRTC_SUCCESS || n == 0)
-    return api_fail(MSS_E_DEVICE, "hiprtcGetCode: %s", hiprtcGetErrorString(r));
 
   mss_sampler s = new (std::nothrow) mss_sampler_s;
   if (!s) return api_fail(MSS_E_NOMEM, "out of host memory");

@@ -50,11 +50,20 @@ __device__ __forceinline__ void field_at(const MssUserField&, const double* __re
 #endif
 }
 
-extern "C" __global__ void __launch_bounds__(256, 2) mss_user_integrate_2(const mss::IntervalGrid g) {
+// Two waves to a SIMD, 256 registers each, unless MSS_USER_ALL_REGISTERS says
+// that the field function leaves too much in scratch memory that way
+// (mss_sampler_create): then one wave with all 512.
+#ifdef MSS_USER_ALL_REGISTERS
+#define MSS_USER_BOUNDS __launch_bounds__(256)
+#else
+#define MSS_USER_BOUNDS __launch_bounds__(256, 2)
+#endif
+
+extern "C" __global__ void MSS_USER_BOUNDS mss_user_integrate_2(const mss::IntervalGrid g) {
   mss::integrate_lanes<2>(MssUserField{}, g);
 }
 
-extern "C" __global__ void __launch_bounds__(256, 2) mss_user_integrate_3(const mss::IntervalGrid g) {
+extern "C" __global__ void MSS_USER_BOUNDS mss_user_integrate_3(const mss::IntervalGrid g) {
   mss::integrate_lanes<3>(MssUserField{}, g);
 }
 
@@ -66,7 +75,7 @@ struct MssUserSource {
   }
 };
 
-extern "C" __global__ void __launch_bounds__(256, 2) mss_user_work_integrate(
+extern "C" __global__ void MSS_USER_BOUNDS mss_user_work_integrate(
     const mss::IntegrateWorkArgs A) {
   mss::work_integrate_loop(A, MssUserSource{});
 }
