@@ -92,23 +92,35 @@ int ilog2(int x) {
 
 // Lane-slice count: minimise the work of the fullest SIMD, its waves times
 // what each does: the fine steps of a lane, the frame's set-up and exit
-// (about one step) and the combination of the slices (0.2 of a step a
-// level).  A SIMD that holds one wave does not reach its issue rate: it
-// takes as long as 1.25 waves' work.  Beyond four waves to a SIMD the rounds
-// overlap and half a wave is left over on average.  Ties go to fewer slices.
-// Over nine shapes (spin-1/2 and spin-1, 1e3 to 1e6 intervals, 10 to 100
-// fine steps) the choice is within 4 % of the best of 1 to 16 slices (spin-1
-// 1e6 x 10: one slice 159 us, two 172; 5e4 x 20 in the lab frame: one 33.9,
-// two 27.5).
-int plan_slices(int64_t K, int32_t L, int cu) {
+// (about one step) and the combination of the slices (`level` of a step a
+// level).  A SIMD that holds few waves does not reach its issue rate: one takes
+// as long as waves[0] waves' work, and so on.  Beyond four waves to a SIMD the
+// rounds overlap and half a wave is left over on average.  Ties go to fewer
+// slices.
+struct SliceCost {
+  double waves[4], level;
+};
+// Launches with a wave for all work.  Over 208 shapes of compiled spin-1/2 and
+// spin-1 fields (1e3 to 1e6 intervals of 3 to 100 fine steps) the choice is
+// within 9 % of the best of 1 to 32 slices, 0.6 % on average (with the costs of
+// the queue 14 % and 0.9 %; 1e5 spin-1/2 intervals of 20 Heun steps: one slice
+// 52 us, four 37).
+constexpr SliceCost kGridCost = {{1.35, 2.1, 3.1, 4.0}, 0.3};
+// Work sets, whose waves take items from a queue: slices cost more there than
+// a grid shows (16 simulations of 1e4 spin-1 intervals of 10 fine steps: one
+// slice 84 us, two 110; as a chained run 157 and 246).
+constexpr SliceCost kQueueCost = {{1.25, 2.0, 3.0, 4.0}, 0.2};
+
+int plan_slices(int64_t K, int32_t L, int cu, const SliceCost& c) {
   const double simds = (double)cu * 4;
   int best = 1;
   double best_cost = 1e300;
   for (int S = 1; S <= 64 && S <= L; S <<= 1) {
     const double per_simd = (double)((K * S + 63) / 64) / simds;
-    const double waves = per_simd <= 1.0 ? 1.25 : per_simd <= 4.0 ? ceil(per_simd) : per_simd + 0.5;
+    const double waves =
+        per_simd <= 4.0 ? c.waves[per_simd > 1.0 ? (int)ceil(per_simd) - 1 : 0] : per_simd + 0.5;
     const double steps = (double)((L + S - 1) / S);
-    const double cost = waves * (steps + 1.0 + 0.2 * ilog2(S));
+    const double cost = waves * (steps + 1.0 + c.level * ilog2(S));
     if (cost < best_cost * (1.0 - 1e-9)) {
       best_cost = cost;
       best = S;
@@ -204,7 +216,7 @@ mss_status validate_problem(const mss_problem* p) {
 
 namespace mss {
 int api_device_cu_count() { return device_cu_count(); }
-int api_plan_slices(int64_t K, int32_t L, int cu) { return plan_slices(K, L, cu); }
+int api_plan_slices(int64_t K, int32_t L, int cu) { return plan_slices(K, L, cu, kQueueCost); }
 int api_ilog2(int x) { return ilog2(x); }
 mss_status api_validate_problem(const mss_problem* p) { return validate_problem(p); }
 bool api_full_basis(const mss_problem* p) {
@@ -224,7 +236,7 @@ mss_status resolve_launch(const mss_problem* p, const mss_launch* in, int* slice
   int S = in ? in->slices : 0;
   int B = in ? in->block : 0;
   const int cu = device_cu_count();
-  if (S == 0) S = plan_slices(p->n_samples, p->n_fine, cu);
+  if (S == 0) S = plan_slices(p->n_samples, p->n_fine, cu, kGridCost);
   if (B == 0 && S >= 1 && S <= 64) {
     // a launch of at most 3 waves per SIMD in all runs its waves at once;
     // one-wave workgroups then spread them evenly over the CUs (four-wave

@@ -46,6 +46,7 @@ mss_status api_validate_terms(int spin_twice, const mss_term* terms, int n_terms
 // sampler reads, and its spin suits the sampler's components
 mss_status api_sampler_check_problem(mss_sampler s, const mss_problem* p);
 int api_device_cu_count();
+// lane-slices of a work set's items
 int api_plan_slices(int64_t K, int32_t L, int cu);
 int api_ilog2(int x);
 // launch shape (lane-slices per interval, block size) of one simulation
