@@ -27,6 +27,7 @@ vector peak) and the CPU oracle's rate on a bounded sample.
 import argparse
 import hashlib
 import json
+import math
 import os
 import statistics
 import sys
@@ -81,8 +82,8 @@ PAPER_CONTEXT = {"workload": "one 100 ms spin-1 sensing simulation, 1e6 CF4 step
 
 
 def spin_one_flops_per_fine_step(tau: int) -> int:
-    """Algorithmic FP64 flops of one spin-1 CF4 fine step by residual
-    squarings (large angles or small tau only): two Lie-Trotter exponentials
+    """Algorithmic FP64 flops of one spin-1 CF4 fine step of the scheme as
+    stated, by residual squarings and whole products: two Lie-Trotter exponentials
     of tau squarings of a complex symmetric 3x3 matrix (six entries: 96 flops
     each, counting a fused multiply-add as two) plus two general 3x3 complex
     products into the interval operator (27 complex multiply-adds = 216 flops
@@ -106,14 +107,20 @@ PRODUCT_FLOPS = 18 * 8
 FULL_PRODUCT_FLOPS = 27 * 8
 
 
+# Square of the largest step angle of the sensing workloads: drives of at most
+# 2,020 Hz over 50 ns, the whole step's weight on one exponential (Euler
+# methods; CF4's are below).
+SENSING_ANGLE_SQUARED = (2.0 * math.pi * 2020.0 * 5e-8) ** 2
+
+
 def spin_one_executed_flops_per_fine_step(tau: int, exponentials: int = 2) -> int:
     """Algorithmic FP64 flops of one spin-1 fine step as executed on the
-    sensing workloads, whose angles (below 2^-6) take the closed form from
-    tau = 20 on; `exponentials` is 2 for CF4 and 1 for the Euler methods.
-    Field samples, frame rotations and angle set-up are not counted."""
-    if tau < 20:
-        return exponentials * (tau * 96 + 216)
-    return exponentials * (SERIES_EXPONENTIAL_FLOPS + PRODUCT_FLOPS)
+    sensing workloads: `exponentials` (2 for CF4 and 1 for the Euler methods)
+    in closed form where all their angles take it, p <= 2^(2 tau - 53), that
+    is from tau = 16 on, by squarings below, and a product into two columns
+    each.  Field samples, frame rotations and angle set-up are not counted."""
+    closed = SENSING_ANGLE_SQUARED <= 2.0 ** (2 * tau - 53)
+    return exponentials * ((SERIES_EXPONENTIAL_FLOPS if closed else tau * 96) + PRODUCT_FLOPS)
 
 
 # Algorithmic FP64 flops of one state update psi_{k+1} = U_k psi_k (spin-1:
