@@ -345,8 +345,9 @@ __device__ __forceinline__ void store_mat(double* __restrict__ p, const Mat<N>& 
 // step is exact for every k; the other two round at the size of r.  Then
 // minimax polynomials of sin r and cos r on |r| <= pi/4, rotated by the
 // quadrant k mod 4.  The polynomials are from a Remez exchange in 60 digits:
-// sin r = r + r y S(y) and cos r = 1 - y / 2 + y^2 C(y), y = r^2, S of degree
-// 5 (relative error 2^-58) and C of degree 5 (2^-64).  4e6 arguments in each
+// sin r = r + r y S(y) and cos r = 1 - y / 2 + y^2 C(y), y = r^2, S and C of
+// degree 5 (with the coefficients rounded as below, sine and cosine to 2^-57
+// and 2^-59 relative).  4e6 arguments in each
 // of |x| < 3, 1e3, 4e5, 1e7 and 1e9 are off by at most 1.7e-16, 3.5e-17 in the
 // mean square, as with the Taylor series to r^17 and r^16 before them, in 3
 // steps less.  (One odd polynomial on |r| <= pi/2 would do without the
@@ -860,8 +861,9 @@ constexpr double kLongSeries = 0.75;
 // instructions against 1,830 at tau = 28 (62 a squaring), and a third of
 // the error (angles of 3e-4: E - I off by 7.1e-20 against 2.1e-19).
 // 4096 spin-1 simulations, 4.5e7 intervals of 10 fine steps in one chained
-// launch: 54.2 ms with the squarings, 9.0 ms with the series; one of 2e5
-// intervals, scan included: 298 and 91 us.
+// launch: 54.2 ms with the squarings, 9.0 ms with the series (7.0 with two
+// columns of the product besides); one of 2e5 intervals, scan included: 298 and
+// 91 us (79).
 template <bool INLINE = false>
 __device__ __forceinline__ void exp_one(const double th[4], int tau, Mat<3>& E) {
   Gen3 g;
@@ -942,8 +944,8 @@ __device__ __forceinline__ bool any_of(const bool (&on)[M]) {
 // component is wanted.  Terms of one component are summed in list order.
 // What bounds the interpreter is the latency of its scalar loads and
 // branches between the sines: 1e6 spin-1 intervals of 10 fine steps, sensing
-// drive, took 391 us with a walk over all terms at every node and take 261
-// (203 with the field compiled in); 3e5 spin-1/2 intervals of 20, 103 and 76.
+// drive, took 391 us with a walk over all terms at every node and take 220
+// (156 with the field compiled in); 3e5 spin-1/2 intervals of 20, 103 and 73.
 template <int C, int M, class Terms>
 __device__ __forceinline__ void field_at(const Terms& fp, const double* __restrict__ params,
                                          const double (&fc)[C], const double (&t)[M],
