@@ -44,14 +44,14 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6  # 256 CU x 2.4 GHz x 128 FP64 flop/clk
 # the sources are unchanged.
 MEASURED_TRAFFIC = {
     ("mss_user_work_chained", "batched_sensing"): {
-        "src": "39b71392e1a59c25",
-        "fetch_kib": 504807.8, "write_kib": 22139089.6,
-        "bytes": int(round((504807.8 * 2.000 + 22139089.6 * 1.000) * 1024)),
+        "src": "77e045795665391e",
+        "fetch_kib": 504816.1, "write_kib": 22138719.7,
+        "bytes": int(round((504816.1 * 2.000 + 22138719.7 * 1.000) * 1024)),
     },
     ("mss_user_work_integrate", "batched_sensing"): {
-        "src": "39b71392e1a59c25",
-        "fetch_kib": 6540.4, "write_kib": 63962252.5,
-        "bytes": int(round((6540.4 * 2.000 + 63962252.5 * 1.000) * 1024)),
+        "src": "77e045795665391e",
+        "fetch_kib": 6064.5, "write_kib": 63958176.7,
+        "bytes": int(round((6064.5 * 2.000 + 63958176.7 * 1.000) * 1024)),
     },
 }
 

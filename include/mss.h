@@ -254,9 +254,10 @@ typedef struct mss_sampler_s* mss_sampler;
 
 /* Compile `source` (NUL-terminated) with n_options extra compiler options
  * (options may be NULL when n_options == 0, e.g. "-DAMP=2.0").  Host only:
- * no GPU is needed.  On success *out owns the compiled code object.  A
- * compile error returns MSS_E_INVALID with the compiler log in
- * mss_last_error() and *out = NULL. */
+ * no GPU is needed.  A function that does not fit the registers of two waves
+ * to a SIMD is compiled a second time for one.  On success *out owns the
+ * compiled code object.  A compile error returns MSS_E_INVALID with the
+ * compiler log in mss_last_error() and *out = NULL. */
 mss_status mss_sampler_create(const char* source, const char* const* options, int32_t n_options,
                               mss_sampler* out);
 

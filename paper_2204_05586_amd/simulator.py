@@ -105,7 +105,10 @@ class Simulator:
                  stream=None, want_spin: bool = False) -> Results:
         """One simulation.  want_spin: also form <J> of every state in the
         last pass of the state product (``Results.spin`` ready, no second
-        read of the states)."""
+        read of the states).  stream: the work runs on it, after what is
+        queued on the current stream; what reads the results is to be ordered
+        after it.  Refused under stream capture (the inputs come from the
+        host)."""
         prob = self.problem(t_start, t_end, dt_integration, dt_output, params, psi0)
         packed = native.PackedProblem(prob)  # once, for the checks and the solve
         native.check(native.lib().mss_validate(packed.ref))
